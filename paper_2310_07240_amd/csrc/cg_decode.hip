@@ -466,10 +466,10 @@ __global__ __launch_bounds__(1024) void decode_kernel(
 //   * delta phase: the delta tables replace the anchor tables in LDS; each group reads back its
 //     anchor's q (requested a group ahead), decodes its nine deltas with epochs before deltas
 //     1 and 6, and stores rows 0..9 (the anchor's fp16 value over the kept q).
-// Both searches start from the 15 fences cum[16 f] of the table in registers (a 4-step select
-// search, no memory round trip), then take three LDS round trips: one 4-ary level and the
-// leaf (each two compare / select steps over entries read together), and the candidate's two
-// bounds, read from its address.
+// Both searches start from fences cum[16 f] in registers (a select search without a memory round
+// trip; the anchors' over all 16 blocks, the deltas' over 16, 8 or 4, see g10_blocks), then take
+// three LDS round trips: one 4-ary level and the leaf (each two compare / select steps over
+// entries read together), and the candidate's two bounds, read from its address.
 constexpr int kG10 = 10;
 constexpr int kAnchorRun = 5;   // anchors per bitstream epoch (a symbol takes <= 18 bits)
 
@@ -486,13 +486,14 @@ struct G10Lane {
   // bits are kept exact: the interval update reads low << lsh + lo_off, and renormalisation
   // uses that sum's bits below the top one (its top bit and that of high = low + hoff - 1 are
   // both off by the same amount, which the xor cancels and the run count masks)
-  uint32_t D, low, lsh, rm1;     // code value - low, low (see above), high - low
+  uint32_t D, low, lsh, R;       // code value - low, low (see above), high - low + 1 (2^32 is 0)
   uint32_t w0, w1, w2, w3;       // the next stream words, w0 partly consumed
   uint32_t avail;                // bits of w0 not yet taken (< 32)
   uint32_t t0, t1, t2, t3;       // the four words after w3, requested one epoch ahead
   uint32_t hcnt;                 // words moved out of w0 since the last epoch (<= 3)
   uint32_t widx;                 // index of t0's word from the stream's first word
   float a;                       // dequantized anchor of the current group
+  uint32_t c0, c1;               // bounds of the candidate (g10_symbol); their low halves stay 0
 };
 
 // Epoch boundary, in two halves: g10_epoch_take replaces the hcnt words dropped from the front
@@ -550,8 +551,8 @@ __device__ __forceinline__ void g10_advance(G10Lane& st, uint32_t lo_off, uint32
   const uint32_t nsh = n1 + f - 1u;
   st.low = low;
   st.lsh = nsh;
-  // high - low + 1 scales by 2^nsh (a result of 2^32 wraps to 0, giving rm1 = 2^32 - 1)
-  st.rm1 = (rsz << nsh) - 1u;
+  // high - low + 1 scales by 2^nsh (a result of 2^32 wraps to 0)
+  st.R = rsz << nsh;
   // D takes the next nsh stream bits: the 32 bits after the taken ones of w0:w1, then a 64-bit
   // shift
   const uint32_t win = __builtin_amdgcn_alignbit(st.w0, st.w1, st.avail);
@@ -607,6 +608,10 @@ struct ColTab {   // all 256 entries in LDS, column layout
   __device__ __forceinline__ int first(int sym, uint32_t, bool down) const {
     return down ? max(sym - 1, 0) : min(sym + 1, CG_NSYM - 1);
   }
+  // first symbol of a centred window of W symbols around symbol c
+  __device__ __forceinline__ static int window(int c, int W) {
+    return min(max(c - W / 2, 0), 256 - W);
+  }
   // the entry's address is tb + 128 sym: pa / 64 - tb / 64 - 254 = 2 sym - 254 exactly
   __device__ __forceinline__ float q2f(uint32_t pa) const {
     return __builtin_fmaf((float)pa, 0.015625f, kc);
@@ -614,17 +619,29 @@ struct ColTab {   // all 256 entries in LDS, column layout
   __device__ __forceinline__ int q_of(uint32_t pa) const { return (int)(pa >> 7) + kqi; }
 };
 
-// Fence registers of a whole table: cum[16 f] << 16 in the high half, and in the low half the
-// byte offset 16 kS (f - 1) of block f - 1 from the lane's entry 0, compared against the
-// target's fixed-point form ti << 16 | fraction; the fence the search ends on carries the
-// block address with it.
-// Entries 0 and 16 (cum[0] = 0 and the total) are never compared and stay zero.
+// Largest symbol i with cum[i] <= ti (four 4-ary levels; entry 255 repeats cum[254]).
 template <class Tab>
-__device__ __forceinline__ void g10_fences(uint32_t (&fT)[17], const Tab& T) {
+__device__ __forceinline__ int g10_find(const Tab& T, uint32_t ti) {
+  int i = 0;
+#pragma unroll 1
+  for (int b = 64; b >= 1; b >>= 2) {
+    const uint32_t x = T.cum(i + b), y = T.cum(i + 2 * b), z = T.cum(i + 3 * b);
+    i += (x <= ti ? b : 0) + (y <= ti ? b : 0) + (z <= ti ? b : 0);
+  }
+  return min(i, CG_NSYM - 1);
+}
+
+// Fence registers of a whole table for a search of kF blocks of 16 symbols from symbol k0 on:
+// fence f is cum[k0 + 16 f] << 16 in the high half, and in the low half the byte offset
+// kS (k0 + 16 (f - 1)) of block f - 1 from the lane's entry 0, compared against the
+// target's fixed-point form ti << 16 | fraction; the fence the search ends on carries the
+// block address with it. Entry 0 is never compared and stays zero.
+template <int kF, class Tab>
+__device__ __forceinline__ void g10_fences(uint32_t (&fT)[kF], const Tab& T, int k0) {
   fT[0] = 0u;
-  fT[16] = 0u;
 #pragma unroll
-  for (int f = 1; f < 16; ++f) fT[f] = (T.cum(16 * f) << 16) | (16u * Tab::kS * (f - 1));
+  for (int f = 1; f < kF; ++f)
+    fT[f] = (T.cum(k0 + 16 * f) << 16) | (Tab::kS * (uint32_t)(k0 + 16 * (f - 1)));
 }
 
 // A table of which only entries k0 .. k1 are in LDS (entry i at byte address rb + 2 i), the
@@ -652,29 +669,68 @@ struct WinTab {
     if (ti >= 65281u + (uint32_t)k1) return min((int)(ti - 65281u), CG_NSYM - 1);
     return down ? max(sym - 1, 0) : min(sym + 1, CG_NSYM - 1);
   }
+  // a whole number of 16-entry blocks, as the stored blocks are
+  __device__ __forceinline__ static int window(int c, int W) {
+    return min(max((c + 8 - W / 2) & ~15, 0), 256 - W);
+  }
 };
 
-// Fences of a window table (blocks g0 .. g1 stored; g1 > g0). The tag of fence f addresses
-// block f - 1 clamped to [g0, g1 - 1], so that the search, which reads block f - 1 or f of the
-// fence it ends on, stays inside the stored blocks. A tag is clamped only when both blocks lie
-// in a flat region (blocks below g0 + 1 and above g1 - 1 hold no frequency other than 1), and a
-// target there misses its candidate and is resolved by the walk's jump.
-__device__ __forceinline__ void g10_fences_win(uint32_t (&fT)[17], const WinTab& T, int g0,
-                                               int g1) {
+// Fences of a window table (blocks g0 .. g1 stored; g1 > g0) for kF blocks from symbol k0 (a
+// multiple of 16) on. The tag of fence f addresses block k0 / 16 + f - 1 clamped to [g0, g1 - 1],
+// so that the search, which reads that block or the next one, stays inside the stored blocks. A
+// tag is clamped only when both blocks lie in a flat region (blocks below g0 + 1 and above
+// g1 - 1 hold no frequency other than 1), and a target there misses its candidate and is
+// resolved by the walk's jump.
+template <int kF>
+__device__ __forceinline__ void g10_fences_win(uint32_t (&fT)[kF], const WinTab& T, int g0,
+                                               int g1, int k0) {
   fT[0] = 0u;
-  fT[16] = 0u;
 #pragma unroll
-  for (int f = 1; f < 16; ++f) {
-    const int blk = min(max(f - 1, g0), g1 - 1);
-    fT[f] = (T.cum(16 * f) << 16) | (32u * (uint32_t)blk);
+  for (int f = 1; f < kF; ++f) {
+    const int blk = min(max((k0 >> 4) + f - 1, g0), g1 - 1);
+    fT[f] = (T.cum(k0 + 16 * f) << 16) | (32u * (uint32_t)blk);
   }
+}
+
+// How many 16-symbol blocks (16, 8 or 4) the wave searches per symbol, and from which symbol k0
+// of its own table each lane does. A search of 8 or 4 blocks around the table's median takes 8
+// or 12 fewer VALU instructions per symbol than one of all 16; a symbol outside them costs the
+// wave a search of the whole table in the walk (as much as about kOutCost instructions, most of
+// it the latency of its dependent LDS reads). The expected
+// cost follows from the tables: `out` is the probability mass outside the blocks, in 2^-16,
+// less the 1 that every symbol's frequency holds whether it occurs or not, summed over the wave
+// (a step of the wave leaves the straight path if any of its lanes does).
+// The kernel is bound by VALU issue (0.96 busy with 70.7 instructions per symbol step on a
+// Mistral-7B-shaped 4K cache); the narrow searches and the high-word products (g10_symbol) took
+// that to 62.7 and the decode from 544 to 518 us there (the deltas of its shallowest third still
+// need all 16 blocks), and from 5770 to 5270 us on a Llama-2-70B-shaped 16K cache with four
+// levels. kOutCost as 110 and 60 (narrow searches for wider tables): 530 and 559 us, 5260 and
+// 5290 us.
+constexpr uint32_t kOutCost = 250;
+template <class Tab>
+__device__ __forceinline__ int g10_blocks(const Tab& T, int& k0) {
+  const int med = g10_find(T, 32768u);
+  auto out = [&](int W) __attribute__((always_inline)) {
+    const int a = Tab::window(med, W), e = a + W;
+    const uint32_t lo = T.cum(a) - (uint32_t)a;
+    const uint32_t hi = e >= CG_NSYM ? 0u : 65281u + (uint32_t)e - T.cum(e);
+    return cg_wave_sum<uint32_t>((lo & 0xFFFFu) + (hi & 0xFFFFu));
+  };
+  const uint32_t c8 = (8u << 16), c4 = (12u << 16);   // instructions saved, times 2^16
+  const uint32_t o8 = out(128) * kOutCost, o4 = out(64) * kOutCost;
+  int kf = 16;
+  if (o8 < c8) kf = 8;
+  if (o4 < c4 && (kf == 16 || c4 - o4 > c8 - o8)) kf = 4;
+  kf = uni(kf);
+  k0 = kf == 16 ? 0 : Tab::window(med, 16 * kf);
+  return kf;
 }
 
 // One symbol under the table T whose entry 0 sits (really, or for a window table virtually) at
 // LDS byte address T.tb, entries T.kS bytes apart, with tagged fences fT. Returns the byte
 // address of the decoded symbol's entry after the interval update and the refill of D.
-template <class Tab>
-__device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)[17],
+template <int kF, class Tab>
+__device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)[kF],
                                                const Tab& T) {
   constexpr uint32_t kS = Tab::kS;
   const uint32_t tb = T.tb;
@@ -688,20 +744,33 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   // (cum << 16 | tag) is <= th iff cum < ti, or cum == ti and tag <= the fraction (a tag is at
   // most 448, so a target exactly on a fence goes to the block below at most once in 146, and
   // the walk takes the one step up).
-  const float te = (float)st.D * (4294966016.0f * __builtin_amdgcn_rcpf((float)st.rm1));
-  const uint32_t th = (uint32_t)te;
+  const float te = (float)st.D * (4294966016.0f * __builtin_amdgcn_rcpf((float)st.R));
+  uint32_t th;   // (R = 0 stands for 2^32: te is then infinite or NaN, converted to some th)
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(th) : "v"(te));
   const uint32_t ti = th >> 16;
-  // binary search over the fences by selects (four compare / select steps)
-  const bool c3 = fT[8] <= th;
-  const uint32_t p4 = c3 ? fT[12] : fT[4];
-  const uint32_t p2a = c3 ? fT[10] : fT[2], p2b = c3 ? fT[14] : fT[6];
-  const uint32_t p1a = c3 ? fT[9] : fT[1], p1b = c3 ? fT[11] : fT[3];
-  const uint32_t p1c = c3 ? fT[13] : fT[5], p1d = c3 ? fT[15] : fT[7];
-  const bool c2 = p4 <= th;
-  const uint32_t p2 = c2 ? p2b : p2a;
-  const uint32_t p1e = c2 ? p1c : p1a, p1f = c2 ? p1d : p1b;
-  const bool c1 = p2 <= th;
-  const uint32_t p1 = c1 ? p1f : p1e;
+  // binary search over the fences by selects (a compare / select step per level)
+  uint32_t p1;
+  if constexpr (kF == 16) {
+    const bool c3 = fT[8] <= th;
+    const uint32_t p4 = c3 ? fT[12] : fT[4];
+    const uint32_t p2a = c3 ? fT[10] : fT[2], p2b = c3 ? fT[14] : fT[6];
+    const uint32_t p1a = c3 ? fT[9] : fT[1], p1b = c3 ? fT[11] : fT[3];
+    const uint32_t p1c = c3 ? fT[13] : fT[5], p1d = c3 ? fT[15] : fT[7];
+    const bool c2 = p4 <= th;
+    const uint32_t p2 = c2 ? p2b : p2a;
+    const uint32_t p1e = c2 ? p1c : p1a, p1f = c2 ? p1d : p1b;
+    const bool c1 = p2 <= th;
+    p1 = c1 ? p1f : p1e;
+  } else if constexpr (kF == 8) {
+    const bool c2 = fT[4] <= th;
+    const uint32_t p2 = c2 ? fT[6] : fT[2];
+    const uint32_t p1a = c2 ? fT[5] : fT[1], p1b = c2 ? fT[7] : fT[3];
+    const bool c1 = p2 <= th;
+    p1 = c1 ? p1b : p1a;
+  } else {
+    static_assert(kF == 4, "16, 8 or 4 blocks");
+    p1 = fT[2] <= th ? fT[3] : fT[1];
+  }
   const bool c0 = p1 <= th;
   // block f = (index of p1) - 1 + c0 starts at byte 16 kS f
   uint32_t qa;
@@ -741,21 +810,31 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   // one three-input add (the compiler would merge the two disjoint constants with an OR first)
   uint32_t pa;
   asm("v_add3_u32 %0, %1, %2, %3" : "=v"(pa) : "v"(qb), "v"(b2 ? 2u * kS : 0u), "v"(b1 ? kS : 0u));
-  uint32_t clo = lds_ld16(pa);
-  const uint32_t chr = lds_ld16(pa + kS);
+  // the bounds as cum << 16, so that an offset (R cum) >> 16 is the high word of one product
+  uint32_t clo = 0u, chi = 0u;
+  if constexpr (kS == 2)
+    asm volatile("ds_read_u16_d16_hi %0, %2\n\tds_read_u16_d16_hi %1, %2 offset:2\n\t"
+                 "s_waitcnt lgkmcnt(0)" : "+v"(st.c0), "+v"(st.c1) : "v"(pa));
+  else
+    asm volatile("ds_read_u16_d16_hi %0, %2\n\tds_read_u16_d16_hi %1, %2 offset:128\n\t"
+                 "s_waitcnt lgkmcnt(0)" : "+v"(st.c0), "+v"(st.c1) : "v"(pa));
   // (the candidate is never the top symbol)
-  uint32_t chi = chr;
-  const uint32_t D = st.D, rm1 = st.rm1;
+  const uint32_t D = st.D, R = st.R;
   // offsets of the candidate's interval from low: [lo_off, hoff) (hoff mod 2^32). The candidate
   // is the symbol iff D - lo_off < hoff - lo_off (unsigned): below lo_off the difference wraps
-  // past the interval's size, which is below 2^32 - lo_off.
-  uint32_t lo_off = scaled_off(rm1, clo);
-  uint32_t hoff = scaled_off(rm1, chi);
+  // past the interval's size, which is below 2^32 - lo_off. With R = 0 (2^32) both offsets come
+  // out 0 and the walk takes the symbol.
+  uint32_t lo_off = __umulhi(R, st.c0);
+  uint32_t hoff = __umulhi(R, st.c1);
   uint32_t d = D - lo_off;
   uint32_t rsz = hoff - lo_off;
   if (d >= rsz) {
     int sym = (int)((pa - tb) / kS);
-    int nxt = T.first(sym, ti, D < lo_off);
+    // the neighbour on D's side; the whole table's candidate where the search covered a part of
+    // the table only or had no target (R = 2^32: the target is D >> 16)
+    const uint32_t rm1 = R - 1u;
+    int nxt = kF < 16 || R == 0u ? g10_find(T, R == 0u ? D >> 16 : ti)
+                                 : T.first(sym, ti, D < lo_off);
     for (int guard = 0; guard < CG_NSYM; ++guard) {
       sym = nxt;
       const int s1 = min(sym + 1, CG_NSYM - 1);
@@ -778,8 +857,8 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
 // One delta token: its symbol under the delta table, dequantized against the group's anchor
 // into row r of the wave's staging buffer.
 // w2 = w / 2 (exact), so 2 q times w2 is the same real number as q times w.
-template <class Tab>
-__device__ __forceinline__ void g10_delta(G10Lane& st, const uint32_t (&fD)[17], const Tab& T,
+template <int kF, class Tab>
+__device__ __forceinline__ void g10_delta(G10Lane& st, const uint32_t (&fD)[kF], const Tab& T,
                                           float w2, uint16_t* obuf, int r, int lane) {
   const uint32_t pa = g10_symbol(st, fD, T);
   obuf[r * 64 + lane] = cg_f2h(st.a + T.q2f(pa) * w2);
@@ -815,17 +894,18 @@ __device__ __forceinline__ void g10_flush(const uint16_t* obuf, uint16_t* row, i
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Rows 0..9 of a whole group of a full, 16-byte aligned 64-channel block: two unconditional
-// 16-byte stores per lane (rows 0..7, then rows 8 and 9, which lanes 16..63 store again with the
-// same bytes as lanes 0..15). With the same two stores on every path, the wait at the next
-// epoch covers only the words it needs, not the stores just issued.
+// Rows 0..9 of a whole group where every octet of channels is whole and 16-byte aligned: two
+// unconditional 16-byte stores per lane (rows 0..7, then rows 8 and 9, which lanes 16..63 store
+// again with the same bytes as lanes 0..15). cc is the lane's octet of the block; in a block of
+// fewer than 64 channels the lanes past its last octet store that octet again. With the same
+// two stores on every path, the wait at the next epoch covers only the words it needs, not the
+// stores just issued.
 __device__ __forceinline__ void g10_flush_full(const uint16_t* obuf, uint16_t* row,
-                                               int64_t rstride, int lane) {
+                                               int64_t rstride, int cc) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int cc = (lane & 7) * 8;
-  const int r0 = lane >> 3, r1 = 8 + ((lane >> 3) & 1);
+  const int r0 = (threadIdx.x & 63) >> 3, r1 = 8 + (r0 & 1);
   const uint4 v0 = *reinterpret_cast<const uint4*>(obuf + r0 * 64 + cc);
   const uint4 v1 = *reinterpret_cast<const uint4*>(obuf + r1 * 64 + cc);
   store_row16(row + r0 * rstride + cc, v0);
@@ -862,15 +942,27 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nwaves = blockDim.x >> 6;
-  const int u = wave % nu, j = wave / nu;             // unit and pair slot of this wave
+  // unit and pair slot of this wave: slot by slot, the units of a slot rotated from one group of
+  // four waves to the next (by 0, 2, 1, 3), so that a SIMD's waves (every fourth wave) work on
+  // different units, those of the first two slots on units two apart
+  const int j = wave / nu;
+  const int rot = (j * nu) >> 2;
+  const int u = (wave + ((rot & 1) << 1 | ((rot >> 1) & 1))) % nu;
   const int ncr = c_end - c_begin;
   const int n_pairs = P.B * ncr;
   const int n_groups = (n_pairs + nw - 1) / nw;
   const int n_units = P.L * 2 * P.nblk;
   int ublk, grp;
-  cg_xcd_map((n_units + nu - 1) / nu, n_groups, ublk, grp);
-  if (ublk * nu >= n_units) return;   // past the last unit block (uniform over the workgroup)
-  const int unit = ublk * nu + u;
+  // A workgroup's units come from different layers (unit u from the u-th part of the units, every
+  // second part backwards), so that deep layers, whose symbols take fewer instructions (see
+  // g10_blocks), share every CU and SIMD with shallow ones.
+  const int n_ublk = (n_units + nu - 1) / nu;
+  cg_xcd_map(n_ublk, n_groups, ublk, grp);
+  if (ublk >= n_ublk) return;   // past the last unit block (uniform over the workgroup)
+  auto unit_of = [&](int uu) __attribute__((always_inline)) {
+    return (uu & 1) ? (uu + 1) * n_ublk - 1 - ublk : uu * n_ublk + ublk;
+  };
+  const int unit = unit_of(u);
   const int cb = unit % P.nblk;
   const int k = (unit / P.nblk) & 1, l = (unit / P.nblk) >> 1;
 
@@ -977,7 +1069,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   if (lane == 0) {
     s_simd[wave] = simd;
     lds_put(&s_left[wave], na);
-    lds_put(&s_wlv[wave], active ? (1 << lv) : 0);
+    lds_put(&s_wlv[j * nu + u], active ? (1 << lv) : 0);
   }
   stage_put(anc_v, anc_d);
   stage_rest(true, kAnchorPre);
@@ -1034,7 +1126,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
       for (int i = 0; i < kStageBatch; ++i) {
         const int rr = (base + i * nwaves) * 2 + half;
         const int t = rr & 63, st = (rr >> 6) % msets, uu = min((rr >> 6) / msets, nu - 1);
-        const int unit2 = ublk * nu + uu;
+        const int unit2 = unit_of(uu);
         const int ch = (unit2 % P.nblk) * 64 + t;
         const int lset = s_level_of_set[uu][st];
         const bool ok = (rr < n_rows) & (unit2 < n_units) & (st < (int)s_nsets[uu]) & (ch < P.C);
@@ -1053,7 +1145,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   auto layout_pass = [&]() __attribute__((always_inline)) {
     if (wave >= nu) return;   // one wave per unit (uniform)
     const int uu = wave;
-    const int unit2 = ublk * nu + uu;
+    const int unit2 = unit_of(uu);
     const int pool = 2 * ustride;
     const bool chok = unit2 < n_units && (unit2 % P.nblk) * 64 + lane < P.C;
     int round = 0, acc = 0;
@@ -1080,7 +1172,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
       for (int i = 0; i < kStageBatch; ++i) {
         const int rr = (base + i * nwaves) * 2 + half;
         const int t = rr & 63, st = (rr >> 6) % msets, uu = min((rr >> 6) / msets, nu - 1);
-        const int unit2 = ublk * nu + uu;
+        const int unit2 = unit_of(uu);
         const int ch = (unit2 % P.nblk) * 64 + t;
         const int lset = s_level_of_set[uu][st];
         const bool ok = (rr < n_rows) & (unit2 < n_units) & (st < (int)s_nsets[uu]) &
@@ -1141,9 +1233,9 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
     const int64_t sidx = cg_stream(P, bclk, chv);
     s = scales[sidx];
     w = P.layer_bin[l] * P.level_mult[lv] * s;
-    uint32_t fA[17];   // tagged fences of the anchor table
+    uint32_t fA[16];   // tagged fences of the anchor table
     const ColTab TA(tab0);
-    g10_fences(fA, TA);
+    g10_fences(fA, TA, 0);
     // bitstream reader: the code value, w1..w3 and the four requested words t0..t3 are the
     // stream's first 8 words; every read stays below offsets[S] + 4 (the requests are clamped
     // to it), inside the readable tail
@@ -1167,7 +1259,8 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
     settle(st.D); settle(st.w0); settle(st.w1); settle(st.w2); settle(st.w3);
     st.low = 0u;
     st.lsh = 0u;
-    st.rm1 = 0xFFFFFFFFu;
+    st.R = 0u;   // 2^32
+    st.c0 = st.c1 = 0u;
     st.a = 0.0f;
 
     // kAnchorRun anchors per epoch. The quantized value q of each anchor goes into the anchor's
@@ -1210,7 +1303,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
     }
   }
 
-  auto delta_groups = [&](const auto& T, const uint32_t (&fD)[17])
+  auto delta_groups = [&](const auto& T, const auto& fD, auto kFull)
                           __attribute__((always_inline)) {
   set_priority(n - na);
   const float w2 = w * 0.5f;
@@ -1228,9 +1321,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   // register a load may still be filling
   float anext = (float)(int)(int16_t)q_of(0) * s;
   uint16_t* row = row0;
-  // whole groups: the loop is written out twice, for full aligned blocks and for the rest
-  const bool full = cbase + 64 <= P.C && (P.C & 7) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-  auto groups = [&](auto kFull) __attribute__((always_inline)) {
+  const int cc = min((lane & 7) * 8, P.C - cbase - 8);   // used where P.C is a multiple of 8
   for (int gi = 0; gi < ngr; ++gi) {
     st.a = anext;
     obuf[lane] = cg_f2h(anext);   // row 0: the anchor's value
@@ -1246,7 +1337,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
     g10_delta(st, fD, T, w2, obuf, 7, lane);
     g10_delta(st, fD, T, w2, obuf, 8, lane);
     g10_delta(st, fD, T, w2, obuf, 9, lane);
-    if constexpr (decltype(kFull)::value) g10_flush_full(obuf, row, rstride, lane);
+    if constexpr (decltype(kFull)::value) g10_flush_full(obuf, row, rstride, cc);
     else g10_flush(obuf, row, rstride, 0, kG10, lane, cbase, P.C);
     row += kG10 * rstride;
     anext = (float)(int)(int16_t)qnext * s;
@@ -1254,9 +1345,6 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
     // instructions; updating after every group measured 1-3 % slower
     if (gi & 1) set_priority((ngr - gi - 1) * (kG10 - 1));
   }
-  };
-  if (full) groups(std::integral_constant<bool, true>{});
-  else groups(std::integral_constant<bool, false>{});
   const int rem = n - ngr * kG10;   // last, partial group (uniform)
   if (rem > 1) {
     st.a = anext;
@@ -1302,20 +1390,39 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   for (int rd = 0; rd < myr; ++rd) round_stage(rd);
   if (myr >= nrounds) return;
   round_stage(myr);
+  // the delta loop is written out per number of searched blocks, and once more, with all 16, for
+  // rows that are not made of whole 16-byte octets of channels
+  const bool full = (P.C & 7) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
   {
     if constexpr (kCompact) {
       const uint32_t d = desc[(u * msets + set) * 64 + lsrc];
       const int g0 = (int)((d >> 20) & 15u), g1 = (int)((d >> 24) & 15u);
       const WinTab T(lds_addr(tabs + u * ustride) + (d & 0xFFFFFu) - 32u * (uint32_t)g0, 16 * g0,
                      16 * (g1 + 1));
-      uint32_t fD[17];
-      g10_fences_win(fD, T, g0, g1);
-      delta_groups(T, fD);
+      int k0;
+      const int kf = full ? g10_blocks(T, k0) : 16;
+      auto groups_of = [&](auto kF, auto kFull) __attribute__((always_inline)) {
+        uint32_t fD[decltype(kF)::value];
+        g10_fences_win(fD, T, g0, g1, decltype(kF)::value == 16 ? 0 : k0);
+        delta_groups(T, fD, kFull);
+      };
+      if (kf == 4) groups_of(std::integral_constant<int, 4>{}, std::true_type{});
+      else if (kf == 8) groups_of(std::integral_constant<int, 8>{}, std::true_type{});
+      else if (full) groups_of(std::integral_constant<int, 16>{}, std::true_type{});
+      else groups_of(std::integral_constant<int, 16>{}, std::false_type{});
     } else {
       const ColTab T(tabs + u * ustride + set * kColSet + lsrc);
-      uint32_t fD[17];
-      g10_fences(fD, T);
-      delta_groups(T, fD);
+      int k0;
+      const int kf = full ? g10_blocks(T, k0) : 16;
+      auto groups_of = [&](auto kF, auto kFull) __attribute__((always_inline)) {
+        uint32_t fD[decltype(kF)::value];
+        g10_fences(fD, T, decltype(kF)::value == 16 ? 0 : k0);
+        delta_groups(T, fD, kFull);
+      };
+      if (kf == 4) groups_of(std::integral_constant<int, 4>{}, std::true_type{});
+      else if (kf == 8) groups_of(std::integral_constant<int, 8>{}, std::true_type{});
+      else if (full) groups_of(std::integral_constant<int, 16>{}, std::true_type{});
+      else groups_of(std::integral_constant<int, 16>{}, std::false_type{});
     }
   }
   for (int rd = myr + 1; rd < nrounds; ++rd) round_stage(rd);
@@ -1336,7 +1443,8 @@ constexpr int kTokRow = 68;    // bytes per lane's symbol row (64 + 4: rows star
 
 // One symbol of a token stream under the staged table `tab` (sentinels from entry 255 on).
 __device__ __forceinline__ uint32_t tok_symbol(G10Lane& st, const uint16_t* tab) {
-  const float te = (float)st.D * (65536.0f * __builtin_amdgcn_rcpf((float)st.rm1));
+  const uint32_t rm1 = st.R - 1u;
+  const float te = (float)st.D * (65536.0f * __builtin_amdgcn_rcpf((float)rm1));
   const uint32_t ti = min((uint32_t)te, 65534u);
   const uint32_t kneg = ~ti;
   const uint16_t* q = tab;
@@ -1351,7 +1459,7 @@ __device__ __forceinline__ uint32_t tok_symbol(G10Lane& st, const uint16_t* tab)
   int sym = (int)((((uint32_t)(uintptr_t)q - (uint32_t)(uintptr_t)tab) >> 1) + cc);
   uint32_t clo = pr & 0xFFFFu;
   uint32_t chi = sym == CG_NSYM - 1 ? CG_TOTAL : pr >> 16;
-  const uint32_t D = st.D, rm1 = st.rm1;
+  const uint32_t D = st.D;
   uint32_t lo_off = scaled_off(rm1, clo);
   uint32_t hoff = scaled_off(rm1, chi);
   uint32_t d = D - lo_off;
@@ -1434,7 +1542,8 @@ __global__ __launch_bounds__(256) void tok_decode_kernel(
   settle(st.D); settle(st.w0); settle(st.w1); settle(st.w2); settle(st.w3);
   st.low = 0u;
   st.lsh = 0u;
-  st.rm1 = 0xFFFFFFFFu;
+  st.R = 0u;   // 2^32
+  st.c0 = st.c1 = 0u;
   st.a = 0.0f;
 
   uint8_t* myrow = &rows[wave][lane * kTokRow];

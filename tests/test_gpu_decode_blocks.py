@@ -1,0 +1,44 @@
+"""The decoder's delta search covers 16, 8 or 4 blocks of 16 symbols, chosen per wave from the
+tables. Payloads coded under another cache's tables hold symbols anywhere in the table, so they
+take every way out of the searched blocks; the oracle decodes the same payload."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2310_07240_amd import workloads as W
+from gpu_helpers import assert_same, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+# bin: the delta bin, which sets the tables' width (the narrower the bin, the wider the table:
+# 0.05 needs all 16 blocks, 0.7 eight, 3 four); channels: whole blocks, a last block of whole
+# octets, and of a broken one; levels over two pairs and 512 units: windowed tables
+@pytest.mark.parametrize("bin_", [0.05, 0.7, 3.0])
+@pytest.mark.parametrize("n_layers,n_channels,n_tokens,chunk_len,levels", [
+    (2, 128, 700, 400, (1.0,)),
+    (1, 72, 95, 95, (1.0,)),
+    (1, 70, 64, 30, (1.0, 2.0)),
+    (4, 4096, 86, 43, (1.0, 4.0)),
+])
+def test_symbols_outside_the_searched_blocks(bin_, n_layers, n_channels, n_tokens, chunk_len,
+                                             levels):
+    w = W.small(name=f"blocks_{bin_}_{n_channels}", n_layers=n_layers, n_tokens=n_tokens,
+                n_channels=n_channels, chunk_len=chunk_len, level_mult=levels,
+                layer_bin=(bin_,) * n_layers, outlier_frac=0.0)
+    shape = oracle.shape_from(w)
+    cl = w.chunk_levels()
+    kv = W.generate(w)
+    ca, cd = oracle.fit_all_levels(kv, shape)
+    # the same cache with a tenth of its tokens replaced by noise of the channel's own range
+    rng = np.random.default_rng(5)
+    other = kv.copy()
+    hit = rng.random(kv.shape) < 0.1
+    top = np.abs(kv.astype(np.float32)).max(axis=3, keepdims=True)
+    other[hit] = (rng.uniform(-1, 1, kv.shape) * top).astype(np.float16)[hit]
+    words, offsets, scales = oracle.encode(other, shape, cl, ca, cd)
+    want = oracle.decode(words, offsets, scales, shape, cl, ca, cd)
+    g = run_gpu(w, kv, decode_oracle_payload=(words, offsets, scales, ca, cd))
+    assert_same("decoded fp16", g["out_from_oracle_payload"], want)
+    assert_same("decoded own payload", g["out"],
+                oracle.decode(g["words"], g["offsets"], g["scales"], shape, cl, ca, cd))
