@@ -57,17 +57,19 @@
 namespace {
 
 constexpr int kMaxWaves = 16;
+constexpr int kPieceWaves = 8;  // waves per workgroup with the tables in the piece layout
 constexpr int kMaxUnits = 16;   // (layer, K/V, channel block) units per workgroup
 // static LDS of the kernel with several units (masks, level maps, SIMD ids, remaining counts);
 // the dynamic LDS budget leaves 1 KB for it
 static_assert(4 * kMaxUnits + 3 * kMaxUnits * CG_MAX_LEVELS + kMaxWaves + 4 * kMaxWaves <= 1024 - 64,
               "static LDS exceeds the reserve");
 constexpr int kStageBatch = 8;  // table-staging loads in flight per lane
-constexpr int kDeltaPre = 8;
-constexpr int kAnchorPre = 12;  // anchor-table loads per lane issued first   // delta-table loads per lane issued before the phase barrier
+constexpr int kDeltaPre = 4;    // delta-table loads per lane issued before the phase barrier
+constexpr int kAnchorPre = 12;  // anchor-table loads per lane issued first
 constexpr size_t kLdsBudget = 160 * 1024 - 1024;   // dynamic LDS per workgroup (CDNA4: 160 KB)
 constexpr int kTabStride = 260;    // u16 per delta table in LDS (256 + 4 pad -> 520 bytes)
 constexpr int kColSet = 260 * 64;  // u16 of a 64-table set in the column layout (rows of 64)
+constexpr int kPieceSet = 33 * 512;  // u16 of a 64-table set in the piece layout (see PieceTab)
 constexpr int kFenceStride = 18;   // u16 per anchor fence row (16 + 2 pad -> 36 bytes)
 constexpr int kEpoch = 4;          // tokens between bitstream requests
 constexpr int kRows = 8;           // decoded token rows staged in LDS per wave before a store
@@ -619,6 +621,23 @@ struct ColTab {   // all 256 entries in LDS, column layout
   __device__ __forceinline__ int q_of(uint32_t pa) const { return (int)(pa >> 7) + kqi; }
 };
 
+// All 256 entries in LDS in 16-byte pieces: entries 8 m .. 8 m + 7 of the lane in column L at byte
+// 16 (64 m + L) of its set, so that a wave's 16-byte reads at 64 different pieces do not
+// collide in the banks. g10_symbol returns the symbol itself for this table.
+struct PieceTab {
+  static constexpr uint32_t kS = 128;   // per entry of a whole number of pieces
+  uint32_t tb;                          // byte address of the lane's piece 0
+  __device__ __forceinline__ uint32_t cum(int i) const {
+    return *(__attribute__((address_space(3))) const uint16_t*)(uintptr_t)(
+        tb + 1024u * (uint32_t)(i >> 3) + 2u * (uint32_t)(i & 7));
+  }
+  __device__ __forceinline__ int first(int sym, uint32_t, bool down) const {
+    return down ? max(sym - 1, 0) : min(sym + 1, CG_NSYM - 1);
+  }
+  __device__ __forceinline__ float q2f(uint32_t sym) const { return (float)(2 * (int)sym - 254); }
+  __device__ __forceinline__ int q_of(uint32_t sym) const { return (int)sym - 127; }
+};
+
 // Largest symbol i with cum[i] <= ti (four 4-ary levels; entry 255 repeats cum[254]).
 template <class Tab>
 __device__ __forceinline__ int g10_find(const Tab& T, uint32_t ti) {
@@ -707,6 +726,8 @@ __device__ __forceinline__ void g10_fences_win(uint32_t (&fT)[kF], const WinTab&
 // levels. kOutCost as 110 and 60 (narrow searches for wider tables): 530 and 559 us, 5260 and
 // 5290 us.
 constexpr uint32_t kOutCost = 250;
+// fewest tokens of a chunk for which the choice pays (it takes about a microsecond)
+constexpr int kNarrowMin = 256;
 template <class Tab>
 __device__ __forceinline__ int g10_blocks(const Tab& T, int& k0) {
   const int med = g10_find(T, 32768u);
@@ -714,7 +735,8 @@ __device__ __forceinline__ int g10_blocks(const Tab& T, int& k0) {
     const int a = Tab::window(med, W), e = a + W;
     const uint32_t lo = T.cum(a) - (uint32_t)a;
     const uint32_t hi = e >= CG_NSYM ? 0u : 65281u + (uint32_t)e - T.cum(e);
-    return cg_wave_sum<uint32_t>((lo & 0xFFFFu) + (hi & 0xFFFFu));
+    const uint32_t sum = cg_dpp_incl_scan<false>((lo & 0xFFFFu) + (hi & 0xFFFFu));
+    return (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
   };
   const uint32_t c8 = (8u << 16), c4 = (12u << 16);   // instructions saved, times 2^16
   const uint32_t o8 = out(128) * kOutCost, o4 = out(64) * kOutCost;
@@ -726,29 +748,28 @@ __device__ __forceinline__ int g10_blocks(const Tab& T, int& k0) {
   return kf;
 }
 
-// One symbol under the table T whose entry 0 sits (really, or for a window table virtually) at
-// LDS byte address T.tb, entries T.kS bytes apart, with tagged fences fT. Returns the byte
-// address of the decoded symbol's entry after the interval update and the refill of D.
-template <int kF, class Tab>
-__device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)[kF],
-                                               const Tab& T) {
-  constexpr uint32_t kS = Tab::kS;
-  const uint32_t tb = T.tb;
-  // th = ti << 16 | (16 fraction bits) from one conversion, ti = th >> 16 the target. The scale
-  // is 2^32 less 5 ulps (5 * 2^8): with D <= rm1, the reciprocal within 1 ulp and two roundings,
-  // te stays below 2^32, so ti <= 65535 needs no clamp. The staged entries 255..259 repeat
-  // cum[254], so a target at or above cum[254] (the top symbol, whose upper bound, the total,
-  // does not fit 16 bits) selects candidate 255, of empty width, and the walk resolves it with
-  // the exact bound. The scale's shortfall of 3e-7 moves ti down by at most 0.02. The entries below
-  // compare against ti as the high half of th (SDWA word selects, no shift); a tagged fence
-  // (cum << 16 | tag) is <= th iff cum < ti, or cum == ti and tag <= the fraction (a tag is at
-  // most 448, so a target exactly on a fence goes to the block below at most once in 146, and
-  // the walk takes the one step up).
+// The target of the lane's next symbol as th = ti << 16 | (16 fraction bits) from one conversion,
+// ti = th >> 16. The scale is 2^32 less 5 ulps (5 * 2^8): with D < R, the reciprocal within 1 ulp
+// and two roundings, te stays below 2^32, so ti <= 65535 needs no clamp. The staged entries
+// 255..259 repeat cum[254], so a target at or above cum[254] (the top symbol, whose upper bound,
+// the total, does not fit 16 bits) selects candidate 255, of empty width, and the walk resolves
+// it with the exact bound. The scale's shortfall of 3e-7 moves ti down by at most 0.02. (R = 0
+// stands for 2^32: te is then infinite or NaN, converted to some th.)
+__device__ __forceinline__ uint32_t g10_target(const G10Lane& st) {
   const float te = (float)st.D * (4294966016.0f * __builtin_amdgcn_rcpf((float)st.R));
-  uint32_t th;   // (R = 0 stands for 2^32: te is then infinite or NaN, converted to some th)
+  uint32_t th;
   asm("v_cvt_u32_f32 %0, %1" : "=v"(th) : "v"(te));
-  const uint32_t ti = th >> 16;
-  // binary search over the fences by selects (a compare / select step per level)
+  return th;
+}
+
+// LDS byte address of the block the target falls in: a binary search over the fences by selects
+// (a compare / select step per level). The table entries compare against ti as the high half of
+// th (SDWA word selects, no shift); a tagged fence (cum << 16 | tag) is <= th iff cum < ti, or
+// cum == ti and tag <= the fraction (a target exactly on a fence may go to the block below it,
+// and the walk takes the one step up).
+template <int kF>
+__device__ __forceinline__ uint32_t g10_block(const uint32_t (&fT)[kF], uint32_t th, uint32_t tb,
+                                              uint32_t kS) {
   uint32_t p1;
   if constexpr (kF == 16) {
     const bool c3 = fT[8] <= th;
@@ -776,6 +797,43 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   uint32_t qa;
   asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 "
       "src1_sel:DWORD" : "=v"(qa) : "v"(p1), "v"(c0 ? tb + 16u * kS : tb));
+  return qa;
+}
+
+// A candidate whose interval does not hold D: from symbol nxt on, one symbol at a time toward D.
+// Returns the symbol and its interval [lo_off, hoff) with d = D - lo_off, rsz = hoff - lo_off.
+template <class Tab>
+__device__ __forceinline__ int g10_walk(const Tab& T, uint32_t D, uint32_t R, int nxt,
+                                        uint32_t& lo_off, uint32_t& hoff, uint32_t& d,
+                                        uint32_t& rsz) {
+  const uint32_t rm1 = R - 1u;
+  int sym = nxt;
+  for (int guard = 0; guard < CG_NSYM; ++guard) {
+    sym = nxt;
+    const int s1 = min(sym + 1, CG_NSYM - 1);
+    const uint32_t clo = T.cum(sym);
+    uint32_t chi = T.cum(s1);
+    chi = sym + 1 >= CG_NSYM ? CG_TOTAL : chi;
+    lo_off = scaled_off(rm1, clo);
+    hoff = scaled_off(rm1, chi);
+    d = D - lo_off;
+    rsz = hoff - lo_off;
+    if (d < rsz) break;
+    nxt = (D < lo_off) ? max(sym - 1, 0) : min(sym + 1, CG_NSYM - 1);
+  }
+  return sym;
+}
+
+// One symbol under the table T whose entry 0 sits (really, or for a window table virtually) at
+// LDS byte address T.tb, entries T.kS bytes apart, with tagged fences fT. Returns the byte
+// address of the decoded symbol's entry after the interval update and the refill of D.
+template <int kF, class Tab>
+__device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)[kF],
+                                               const Tab& T) {
+  constexpr uint32_t kS = Tab::kS;
+  const uint32_t tb = T.tb;
+  const uint32_t th = g10_target(st), ti = th >> 16;
+  const uint32_t qa = g10_block(fT, th, tb, kS);
   // 4-ary level: cum[16 f + 4 m], m = 1..3
   // two steps over the three sorted entries: cum[16 f + 8], then cum[16 f + 12] or cum[16 f + 4]
   bool b8, b4;
@@ -811,7 +869,6 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   uint32_t pa;
   asm("v_add3_u32 %0, %1, %2, %3" : "=v"(pa) : "v"(qb), "v"(b2 ? 2u * kS : 0u), "v"(b1 ? kS : 0u));
   // the bounds as cum << 16, so that an offset (R cum) >> 16 is the high word of one product
-  uint32_t clo = 0u, chi = 0u;
   if constexpr (kS == 2)
     asm volatile("ds_read_u16_d16_hi %0, %2\n\tds_read_u16_d16_hi %1, %2 offset:2\n\t"
                  "s_waitcnt lgkmcnt(0)" : "+v"(st.c0), "+v"(st.c1) : "v"(pa));
@@ -829,29 +886,67 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   uint32_t d = D - lo_off;
   uint32_t rsz = hoff - lo_off;
   if (d >= rsz) {
-    int sym = (int)((pa - tb) / kS);
+    const int sym = (int)((pa - tb) / kS);
     // the neighbour on D's side; the whole table's candidate where the search covered a part of
     // the table only or had no target (R = 2^32: the target is D >> 16)
-    const uint32_t rm1 = R - 1u;
-    int nxt = kF < 16 || R == 0u ? g10_find(T, R == 0u ? D >> 16 : ti)
+    const int nxt = kF < 16 || R == 0u ? g10_find(T, R == 0u ? D >> 16 : ti)
                                  : T.first(sym, ti, D < lo_off);
-    for (int guard = 0; guard < CG_NSYM; ++guard) {
-      sym = nxt;
-      const int s1 = min(sym + 1, CG_NSYM - 1);
-      clo = T.cum(sym);
-      chi = T.cum(s1);
-      chi = sym + 1 >= CG_NSYM ? CG_TOTAL : chi;
-      lo_off = scaled_off(rm1, clo);
-      hoff = scaled_off(rm1, chi);
-      d = D - lo_off;
-      rsz = hoff - lo_off;
-      if (d < rsz) break;
-      nxt = (D < lo_off) ? max(sym - 1, 0) : min(sym + 1, CG_NSYM - 1);
-    }
-    pa = tb + kS * (uint32_t)sym;
+    pa = tb + kS * (uint32_t)g10_walk(T, D, R, nxt, lo_off, hoff, d, rsz);
   }
   g10_advance(st, lo_off, hoff, d, rsz);
   return pa;
+}
+
+// The same for a table in the piece layout, where the chain of one symbol is what counts (a SIMD
+// runs one wave, see cg_launch_decode): the block's 16 entries and the one after them come
+// in one LDS round trip, and the search and the candidate's bounds are selects on registers (one
+// round trip per symbol instead of three, for about eight more instructions). Returns the symbol.
+__device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)[16],
+                                               const PieceTab& T) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) const u32x4 lds_cu32x4;
+  const uint32_t th = g10_target(st), ti = th >> 16;
+  const uint32_t qa = g10_block(fT, th, T.tb, PieceTab::kS);
+  // entries 2 k and 2 k + 1 of the block in the halves of e[k], entry 16 in e8
+  const u32x4 e03 = *(lds_cu32x4*)(uintptr_t)qa, e47 = *(lds_cu32x4*)(uintptr_t)(qa + 1024u);
+  const uint32_t e8 = lds_ld16(qa + 2048u);
+  // the largest i with entry i <= ti (entry 0 is), a bit at a time; x4, x2: the dwords of the
+  // entries compared, pl: the dword holding entry i, pn: the next one
+  const bool b8 = (e47.x & 0xFFFFu) <= ti;
+  const uint32_t x4 = b8 ? e47.z : e03.z;
+  const bool b4 = (x4 & 0xFFFFu) <= ti;
+  const uint32_t xa = b8 ? e47.y : e03.y, xb = b8 ? e47.w : e03.w;
+  const uint32_t x2 = b4 ? xb : xa;
+  const bool b2 = (x2 & 0xFFFFu) <= ti;
+  const uint32_t y = b4 ? x4 : (b8 ? e47.x : e03.x);
+  const uint32_t z = b4 ? (b8 ? e8 : e47.x) : x4;
+  const uint32_t pl = b2 ? x2 : y, pn = b2 ? z : x2;
+  const bool b1 = (pl >> 16) <= ti;
+  const uint32_t pair = __builtin_amdgcn_alignbit(pn, pl, b1 ? 16u : 0u);
+  const uint32_t i = (b8 ? 8u : 0u) + (b4 ? 4u : 0u) + (b2 ? 2u : 0u) + (b1 ? 1u : 0u);
+  uint32_t sym = ((qa - T.tb) >> 7) + i;
+  const uint32_t D = st.D, R = st.R;
+  uint32_t lo_off = __umulhi(R, pair << 16);
+  uint32_t hoff = __umulhi(R, pair & 0xFFFF0000u);
+  uint32_t d = D - lo_off;
+  uint32_t rsz = hoff - lo_off;
+  if (d >= rsz) {
+    const int nxt = R == 0u ? g10_find(T, D >> 16) : T.first((int)sym, ti, D < lo_off);
+    sym = (uint32_t)g10_walk(T, D, R, nxt, lo_off, hoff, d, rsz);
+  }
+  g10_advance(st, lo_off, hoff, d, rsz);
+  return sym;
+}
+
+// The first symbol of a stream, whose interval is the whole 2^32: its target is D >> 16 and its
+// offsets are cum << 16. Returns the quantized value.
+template <class Tab>
+__device__ __forceinline__ int g10_first(G10Lane& st, const Tab& T) {
+  const int sym = g10_find(T, st.D >> 16);
+  const uint32_t lo_off = T.cum(sym) << 16;
+  const uint32_t hoff = sym == CG_NSYM - 1 ? 0u : T.cum(sym + 1) << 16;
+  g10_advance(st, lo_off, hoff, st.D - lo_off, hoff - lo_off);
+  return sym - 127;
 }
 
 // One delta token: its symbol under the delta table, dequantized against the group's anchor
@@ -919,12 +1014,16 @@ __device__ __forceinline__ void g10_flush_full(const uint16_t* obuf, uint16_t* r
 // ustride u16 (at least one whole table set), which holds its anchor tables in the anchor phase
 // and then the windows of its delta tables, packed; sets that do not fit together are staged in
 // rounds, one after the other. Otherwise the region holds min(nw, levels) whole sets.
-template <bool kCompact>
-__global__ __launch_bounds__(1024) void decode_g10_kernel(
+// kPiece: whole sets in the piece layout, for calls of at most one wave per SIMD; the workgroup
+// then has more waves than the nu nw that decode (helpers: they only stage tables).
+enum class Stage { kColumns, kWindows, kPieces };
+template <Stage kStage>
+__global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024) void decode_g10_kernel(
     KParams P, const uint32_t* __restrict__ words, const uint64_t* __restrict__ offsets,
     const float* __restrict__ scales, const uint8_t* __restrict__ chunk_level,
     const uint16_t* __restrict__ cdfA, const uint16_t* __restrict__ cdfD, int c_begin,
     int c_end, int nw, int nu, int ustride, uint16_t* __restrict__ out) {
+  constexpr bool kCompact = kStage == Stage::kWindows, kPiece = kStage == Stage::kPieces;
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   __shared__ int s_wlv[kMaxWaves];               // bit of the level of each wave's pair (0: none)
   __shared__ uint8_t s_set_of_level[kMaxUnits][CG_MAX_LEVELS];
@@ -942,6 +1041,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nwaves = blockDim.x >> 6;
+  const int ns = kPiece ? nwaves / nu : nw;   // waves per unit, those past nw helpers
   // unit and pair slot of this wave: slot by slot, the units of a slot rotated from one group of
   // four waves to the next (by 0, 2, 1, 3), so that a SIMD's waves (every fourth wave) work on
   // different units, those of the first two slots on units two apart
@@ -953,14 +1053,18 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   const int n_groups = (n_pairs + nw - 1) / nw;
   const int n_units = P.L * 2 * P.nblk;
   int ublk, grp;
-  // A workgroup's units come from different layers (unit u from the u-th part of the units, every
-  // second part backwards), so that deep layers, whose symbols take fewer instructions (see
-  // g10_blocks), share every CU and SIMD with shallow ones.
+  // Where the grid is one round on the CUs, its slowest workgroup is its end: a workgroup's units
+  // then come from different layers (unit u from the u-th part of the units, every second part
+  // backwards), so that deep layers, whose symbols take fewer instructions (see g10_blocks),
+  // share every CU and SIMD with shallow ones (Mistral-7B-shaped 4K cache: 515 us, 527 without).
+  // Else, and where blocks of 64 channels share cache lines with their neighbours, neighbouring
+  // units: their rows are stored together (384 workgroups of 4096 channels: 763 us, 804 mixed).
+  const bool mix = !kCompact && (P.C & 63) == 0 && gridDim.x <= 256u;
   const int n_ublk = (n_units + nu - 1) / nu;
   cg_xcd_map(n_ublk, n_groups, ublk, grp);
   if (ublk >= n_ublk) return;   // past the last unit block (uniform over the workgroup)
   auto unit_of = [&](int uu) __attribute__((always_inline)) {
-    return (uu & 1) ? (uu + 1) * n_ublk - 1 - ublk : uu * n_ublk + ublk;
+    return !mix ? ublk * nu + uu : (uu & 1) ? (uu + 1) * n_ublk - 1 - ublk : uu * n_ublk + ublk;
   };
   const int unit = unit_of(u);
   const int cb = unit % P.nblk;
@@ -968,13 +1072,13 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
 
   // Stage whole tables into LDS in the column layout (entry i of channel cb * 64 + L at u16
   // 64 i + L of its set): the anchor tables of every unit (set 0), or the delta tables of the
-  // levels each unit's pairs use. The nw waves of a unit stage that unit's tables; a load
+  // levels each unit's pairs use. The ns waves of a unit stage that unit's tables; a load
   // instruction covers the 16 columns of one residue mod 4, four neighbouring lanes taking four
   // consecutive 16-byte pieces (entries 8 p .. 8 p + 7) of one table, so it touches 16 half
   // cache lines and its column stores put four lanes on a bank (with one lane per table the
   // 64 cache lines of every load made the staging slower, with eight the stores conflicted
   // eight ways). Instruction z of a set (32 of them) takes the columns c with c mod 4 = z mod 4
-  // and pieces 4 ((z mod 32) / 4) + (0 .. 3); wave slot j takes instructions j, j + nw, ... of
+  // and pieces 4 ((z mod 32) / 4) + (0 .. 3); wave slot j takes instructions j, j + ns, ... of
   // the unit's sets (set and instruction uniform). stage_issue
   // loads batch i0 .. i0 + N - 1 into registers, stage_put writes them (eight 2-byte stores a
   // piece); the first anchor batch
@@ -984,7 +1088,9 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   const int half = lane >> 5, piece = lane & 31;
   const bool unit_ok = unit < n_units;
   const int64_t lk_row = (int64_t)(l * 2 + k) * P.C + cb * 64;   // table row of channel cb*64
-  const int pcol = ((lane >> 2) << 2);   // the first column of the lane's group of four
+  // (piece layout: 16 consecutive columns an instruction, so that the 16-byte stores of a piece go
+  // to different banks)
+  const int pcol = kPiece ? lane >> 2 : ((lane >> 2) << 2);
   // levels used by this wave's unit, a bit per level (set after the first barrier); the set of
   // a level is its rank among them
   uint32_t umask = 0u;
@@ -1002,14 +1108,16 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
     for (int i = 0; i < N; ++i) {
       // unconditional loads (a piece that is not staged reads the first table instead), so
       // that all of them are in flight before the first store waits
-      const int z = uni(j + nw * (i0 + i));      // load instruction of the unit's sets
+      const int z = uni(j + ns * (i0 + i));      // load instruction of the unit's sets
       const int st = uni(z >> 5);
-      const int col = pcol + (z & 3), pc = ((z & 31) >> 2) * 4 + (lane & 3);
+      const int col = pcol + (kPiece ? 16 : 1) * (z & 3), pc = ((z & 31) >> 2) * 4 + (lane & 3);
       const int lset = anchors ? 0 : level_of_set(st);
       const bool ok = (st < sets) & unit_ok & (cb * 64 + col < P.C);
       const int64_t trow = lk_row + col + (anchors ? 0 : (int64_t)lset * P.L * 2 * P.C);
       v[i] = reinterpret_cast<const uint4*>(srcbase + (ok ? trow : 0) * 256)[pc];
-      dsto[i] = ok ? u * ustride + st * kColSet + pc * 8 * 64 + col : -1;
+      dsto[i] = !ok ? -1
+                : kPiece ? u * ustride + st * kPieceSet + (pc * 64 + col) * 8
+                         : u * ustride + st * kColSet + pc * 8 * 64 + col;
     }
   };
   auto stage_put = [&](const auto& v, const auto& dsto) __attribute__((always_inline)) {
@@ -1019,8 +1127,16 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
       if (dsto[i] < 0) continue;
       uint16_t* dst = tabs + dsto[i];
       const uint4 x = v[i];
-      const bool last = ((dsto[i] - u * ustride) % kColSet) >= 31 * 8 * 64;   // entries 248..
+      constexpr int kSet = kPiece ? kPieceSet : kColSet;
+      const bool last = ((dsto[i] - u * ustride) % kSet) >= 31 * 8 * 64;   // entries 248..
       const uint32_t top = x.w & 0xFFFFu;   // cum[254] in piece 31
+      if constexpr (kPiece) {
+        *reinterpret_cast<uint4*>(dst) = make_uint4(x.x, x.y, x.z, last ? top * 0x10001u : x.w);
+        if (last)   // piece 32: entries 256..263
+          *reinterpret_cast<uint4*>(dst + 512) =
+              make_uint4(top * 0x10001u, top * 0x10001u, top * 0x10001u, top * 0x10001u);
+        continue;
+      }
       dst[0 * 64] = (uint16_t)x.x;
       dst[1 * 64] = (uint16_t)(x.x >> 16);
       dst[2 * 64] = (uint16_t)x.y;
@@ -1038,7 +1154,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   // the batches from i0 on
   auto stage_rest = [&](bool anchors, int i0) __attribute__((always_inline)) {
     const int pairs = (anchors ? 1 : __builtin_popcount(umask)) * 32;
-    for (int i = i0; j + nw * i < pairs; i += kStageBatch) {
+    for (int i = i0; j + ns * i < pairs; i += kStageBatch) {
       uint4 v[kStageBatch];
       int dsto[kStageBatch];
       stage_issue(anchors, i, v, dsto);
@@ -1053,7 +1169,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   const uint64_t total = offsets[P.S];
 
   const int pair = uni(grp * nw + j);
-  const bool active = unit_ok && pair < n_pairs;
+  const bool active = unit_ok && j < nw && pair < n_pairs;
   // pairs chunk-major: the waves of a workgroup decode the same chunk of consecutive contexts,
   // so they have the same token count and finish together
   const int b = uni(active ? pair % P.B : 0);
@@ -1069,7 +1185,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   if (lane == 0) {
     s_simd[wave] = simd;
     lds_put(&s_left[wave], na);
-    lds_put(&s_wlv[j * nu + u], active ? (1 << lv) : 0);
+    if (j < nw) lds_put(&s_wlv[j * nu + u], active ? (1 << lv) : 0);
   }
   stage_put(anc_v, anc_d);
   stage_rest(true, kAnchorPre);
@@ -1221,7 +1337,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
   const int chv = cb * 64 + lsrc;
   const int64_t rstride = P.C;
   uint16_t* row0 = out + cg_elem(P, b, l, k, tok0, cb * 64);   // token tok0, channel cb * 64
-  const uint16_t* tab0 = tabs + u * ustride + lsrc;   // anchor table of the lane (column)
+  const uint16_t* tab0 = tabs + u * ustride + (kPiece ? 8 : 1) * lsrc;   // the lane's anchor table
   G10Lane st;
   const uint32_t* sbase = words;
   uint32_t cap = 0;
@@ -1234,7 +1350,10 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
     s = scales[sidx];
     w = P.layer_bin[l] * P.level_mult[lv] * s;
     uint32_t fA[16];   // tagged fences of the anchor table
-    const ColTab TA(tab0);
+    const auto TA = [&] {
+      if constexpr (kPiece) return PieceTab{lds_addr(tab0)};
+      else return ColTab(tab0);
+    }();
     g10_fences(fA, TA, 0);
     // bitstream reader: the code value, w1..w3 and the four requested words t0..t3 are the
     // stream's first 8 words; every read stays below offsets[S] + 4 (the requests are clamped
@@ -1286,7 +1405,8 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
       g10_epoch_request(st, sbase, cap);
 #pragma unroll
       for (int r = 0; r < kAnchorRun; ++r)
-        if (g0 + r < na) qrun[r] = TA.q_of(g10_symbol(st, fA, TA));
+        if (r == 0 && g0 == 0) qrun[r] = g10_first(st, TA);
+        else if (g0 + r < na) qrun[r] = TA.q_of(g10_symbol(st, fA, TA));
       // every other run (the ranking reads three LDS words and takes a dozen scalar
       // instructions)
       if ((g0 / kAnchorRun) & 1) set_priority(max(na - g0 - kAnchorRun, 0));
@@ -1400,7 +1520,7 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
       const WinTab T(lds_addr(tabs + u * ustride) + (d & 0xFFFFFu) - 32u * (uint32_t)g0, 16 * g0,
                      16 * (g1 + 1));
       int k0;
-      const int kf = full ? g10_blocks(T, k0) : 16;
+      const int kf = full && n >= kNarrowMin ? g10_blocks(T, k0) : 16;
       auto groups_of = [&](auto kF, auto kFull) __attribute__((always_inline)) {
         uint32_t fD[decltype(kF)::value];
         g10_fences_win(fD, T, g0, g1, decltype(kF)::value == 16 ? 0 : k0);
@@ -1410,10 +1530,16 @@ __global__ __launch_bounds__(1024) void decode_g10_kernel(
       else if (kf == 8) groups_of(std::integral_constant<int, 8>{}, std::true_type{});
       else if (full) groups_of(std::integral_constant<int, 16>{}, std::true_type{});
       else groups_of(std::integral_constant<int, 16>{}, std::false_type{});
+    } else if constexpr (kPiece) {
+      const PieceTab T{lds_addr(tabs + u * ustride + set * kPieceSet + 8 * lsrc)};
+      uint32_t fD[16];
+      g10_fences(fD, T, 0);
+      if (full) delta_groups(T, fD, std::true_type{});
+      else delta_groups(T, fD, std::false_type{});
     } else {
       const ColTab T(tabs + u * ustride + set * kColSet + lsrc);
       int k0;
-      const int kf = full ? g10_blocks(T, k0) : 16;
+      const int kf = full && n >= kNarrowMin ? g10_blocks(T, k0) : 16;
       auto groups_of = [&](auto kF, auto kFull) __attribute__((always_inline)) {
         uint32_t fD[decltype(kF)::value];
         g10_fences(fD, T, decltype(kF)::value == 16 ? 0 : k0);
@@ -1677,29 +1803,67 @@ hipError_t cg_launch_decode(const KParams& P, const uint32_t* words, const uint6
            (size_t)(nuc + 1) * (rows + set_bytes + desc_bytes) <= kLdsBudget &&
            (n_units + nuc) / (nuc + 1) * n_groups >= 256)
       ++nuc;
-    const bool compact = msets > 1 && nuc > nu;
+    // Up to one wave per SIMD (a chunk of a cache as it arrives, a short context), the time is the
+    // latency of the symbols' chain: the piece layout takes one LDS round trip per symbol instead
+    // of three (the second chunk of a Mistral-7B-shaped cache, 1024 waves: 472 -> 399 us; 16 waves
+    // of 256 tokens: 91 -> 77 us). With two waves per SIMD they hide each other's round trips
+    // and the search with fewer instructions is the faster one. The smallest workgroups that
+    // make one round on 256 CUs, at most four decoding waves each: pnw pairs x pnu units.
+    int pnw = 0, pnu = 0;
+    auto piece_lds = [&](int w, int un) {
+      return (size_t)un * (w * kG10 * 64 + (w < P.NLV ? w : P.NLV) * kPieceSet) * sizeof(uint16_t);
+    };
+    const int n_max = P.CL < P.T ? P.CL : P.T;
+    // (short chunks of several contexts are left: their time is the staging of tables, which
+    // more pairs of a unit would share)
+    for (int waves = 1; waves <= 4 && !pnw && (n_pairs == 1 || n_max >= 40); ++waves)
+      for (int w = 1; w <= waves && w <= n_pairs; ++w) {
+        const int un = waves / w;
+        if (un * w == waves && piece_lds(w, un) <= kLdsBudget &&
+            (n_units + un - 1) / un * ((n_pairs + w - 1) / w) <= 256) {
+          pnw = w;
+          pnu = un;   // the last fit: more pairs of a unit share its tables
+        }
+      }
+    bool compact = msets > 1 && nuc > nu;
+    if (!pnw && !compact && nw * nu <= 4 && piece_lds(nw, nu) <= kLdsBudget) {
+      // more waves than that, but the tables leave room for four on a CU (one chunk of 1305
+      // tokens, 12 x 4096 channels: 760 -> 676 us)
+      pnw = nw;
+      pnu = nu;
+    }
+    const bool piece = pnw > 0;
+    compact = compact && !piece;
     int units = nu, ustride = (int)((size_t)msets * 64 * kTabStride);
+    int waves = nw * nu;
     size_t lds = lds_for(nw, nu);
+    int pairs_wg = nw;
+    if (piece) {
+      pairs_wg = pnw;
+      units = pnu;
+      ustride = (pnw < P.NLV ? pnw : P.NLV) * kPieceSet;
+      lds = piece_lds(pnw, pnu);
+      waves = kPieceWaves / pnu * pnu;   // those past pnw pnu only stage tables
+    }
     if (compact) {
       units = nuc;
+      waves = nw * nuc;
       // each unit's region: what the LDS budget leaves, in 16-byte multiples
       const size_t per_unit = kLdsBudget / (size_t)nuc - rows - desc_bytes;
       ustride = (int)((per_unit & ~(size_t)15) / sizeof(uint16_t));
       lds = (size_t)nuc * (rows + desc_bytes) + (size_t)nuc * ustride * sizeof(uint16_t);
     }
-    const int64_t grid = cg_xcd_grid((n_units + units - 1) / units, n_groups);
-    const void* kfn = compact ? (const void*)decode_g10_kernel<true>
-                              : (const void*)decode_g10_kernel<false>;
-    hipError_t e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const int64_t grid = cg_xcd_grid((n_units + units - 1) / units,
+                                     (n_pairs + pairs_wg - 1) / pairs_wg);
+    const auto kernel = piece     ? &decode_g10_kernel<Stage::kPieces>
+                        : compact ? &decode_g10_kernel<Stage::kWindows>
+                                  : &decode_g10_kernel<Stage::kColumns>;
+    hipError_t e = hipFuncSetAttribute((const void*)kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    if (compact)
-      hipLaunchKernelGGL(decode_g10_kernel<true>, dim3((unsigned)grid), dim3(64 * nw * units), lds,
-                         st, P, words, offsets, scales, chunk_level, cdf_anchor, cdf_delta,
-                         c_begin, c_end, nw, units, ustride, out);
-    else
-      hipLaunchKernelGGL(decode_g10_kernel<false>, dim3((unsigned)grid), dim3(64 * nw * units),
-                         lds, st, P, words, offsets, scales, chunk_level, cdf_anchor, cdf_delta,
-                         c_begin, c_end, nw, units, ustride, out);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * waves), lds, st, P, words, offsets,
+                       scales, chunk_level, cdf_anchor, cdf_delta, c_begin, c_end, pairs_wg, units,
+                       ustride, out);
     return hipGetLastError();
   }
   const int64_t grid = cg_xcd_grid(n_units, n_groups);

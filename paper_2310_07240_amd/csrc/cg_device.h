@@ -123,14 +123,20 @@ __device__ __forceinline__ int64_t tok_stream(const KParams& P, int b, int c, in
 // a CU that finished a short workgroup waited for the next long one ahead of its own in the
 // queue). Unit blocks are numbered to a multiple of 8 per pair group, so all pair groups of a
 // unit block run on one XCD (its tables stay in that XCD's L2); blocks past n_ublk must leave.
+// Grids of one round on the 256 CUs are not padded: the empty blocks would leave some XCDs with
+// two workgroups for some of their CUs and others with too few (19 pair groups x 13 unit blocks of
+// a decode: 613 us padded, 403 us dense).
+__host__ __device__ __forceinline__ int64_t cg_xcd_pad(int64_t n_ublk, int64_t n_groups) {
+  return n_ublk * n_groups <= 256 ? n_ublk : (n_ublk + 7) / 8 * 8;
+}
 __device__ __forceinline__ void cg_xcd_map(int n_ublk, int n_groups, int& ublk, int& grp) {
-  const int pad = n_groups == 1 ? n_ublk : (n_ublk + 7) / 8 * 8;
+  const int pad = n_groups == 1 ? n_ublk : (int)cg_xcd_pad(n_ublk, n_groups);
   const int b = (int)blockIdx.x;
   grp = b / pad;
   ublk = b - grp * pad;
 }
 inline int64_t cg_xcd_grid(int64_t n_ublk, int64_t n_groups) {
-  return n_groups == 1 ? n_ublk : (n_ublk + 7) / 8 * 8 * n_groups;
+  return n_groups == 1 ? n_ublk : cg_xcd_pad(n_ublk, n_groups) * n_groups;
 }
 
 // Window of a cumulative table held by 32 lanes of a wave, 16 bytes (8 entries) each: piece p
@@ -196,6 +202,23 @@ __device__ __forceinline__ uint64_t cg_wave_incl_scan64(uint64_t v) {
     uint64_t n = __shfl_up(v, o, 64);
     if (lane >= o) v += n;
   }
+  return v;
+}
+
+// Inclusive prefix of v over the 64 lanes with DPP moves (no LDS): a Hillis-Steele scan inside
+// each row of 16 lanes (row_shr 1, 2, 4, 8, zero from outside the row), then lane 15 of rows 0
+// and 2 into rows 1 and 3 (row_bcast:15) and lane 31 into rows 2 and 3 (row_bcast:31). kMax
+// takes the running maximum instead of the sum (values must be non-negative). Lane 63 ends with
+// the whole wave's sum or maximum.
+template <bool kMax>
+__device__ __forceinline__ uint32_t cg_dpp_incl_scan(uint32_t v) {
+  auto op = [](uint32_t a, uint32_t b) { return kMax ? max(a, b) : a + b; };
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
   return v;
 }
 

@@ -130,23 +130,6 @@ __device__ void normalize_wave(const CountT* cnt, uint16_t* out, int shift = -1)
   reinterpret_cast<uint64_t*>(out)[lane] = packed;
 }
 
-// Inclusive prefix of v over the 64 lanes with DPP moves (no LDS): a Hillis-Steele scan inside
-// each row of 16 lanes (row_shr 1, 2, 4, 8, zero from outside the row), then lane 15 of rows 0
-// and 2 into rows 1 and 3 (row_bcast:15) and lane 31 into rows 2 and 3 (row_bcast:31). kMax
-// takes the running maximum instead of the sum (values must be non-negative). Lane 63 ends with
-// the whole wave's sum or maximum.
-template <bool kMax>
-__device__ __forceinline__ uint32_t dpp_incl_scan(uint32_t v) {
-  auto op = [](uint32_t a, uint32_t b) { return kMax ? max(a, b) : a + b; };
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
-  return v;
-}
-
 // normalize_wave for 16-bit counts (the 16-bit field at bit `shift` of each word) whose total
 // is below 2^16, as the fit's 16-bit kernels guarantee: the same tables from 32-bit arithmetic.
 // Every product c (2^16 - 255) and q N stays below 2^32 (c, N <= 65535; q <= 2^16 - 254), so the
@@ -163,7 +146,7 @@ __device__ void normalize16_wave(const uint32_t* cnt, uint16_t* out, int shift) 
     c[j] = i < CG_NSYM ? (cnt[i] >> shift) & 0xFFFFu : 0u;
     local += c[j];
   }
-  uint32_t N = (uint32_t)__builtin_amdgcn_readlane((int)dpp_incl_scan<false>(local), 63);
+  uint32_t N = (uint32_t)__builtin_amdgcn_readlane((int)cg_dpp_incl_scan<false>(local), 63);
   if (N == 0) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) c[j] = (lane * 4 + j) < CG_NSYM ? 1u : 0u;
@@ -176,7 +159,7 @@ __device__ void normalize16_wave(const uint32_t* cnt, uint16_t* out, int shift) 
     const int i = lane * 4 + j;
     if (i < CG_NSYM) key = max(key, (c[j] << 8) | (uint32_t)(255 - i));
   }
-  const uint32_t kmax = (uint32_t)__builtin_amdgcn_readlane((int)dpp_incl_scan<true>(key), 63);
+  const uint32_t kmax = (uint32_t)__builtin_amdgcn_readlane((int)cg_dpp_incl_scan<true>(key), 63);
   const int besti = 255 - (int)(kmax & 0xFFu);
   const float ratio = (float)kSpread / (float)N;
   uint32_t f[4];
@@ -191,12 +174,12 @@ __device__ void normalize16_wave(const uint32_t* cnt, uint16_t* out, int shift) 
     f[j] = lane * 4 + j < CG_NSYM ? 1u + q : 0u;
     fl += f[j];
   }
-  const uint32_t sumf = (uint32_t)__builtin_amdgcn_readlane((int)dpp_incl_scan<false>(fl), 63);
+  const uint32_t sumf = (uint32_t)__builtin_amdgcn_readlane((int)cg_dpp_incl_scan<false>(fl), 63);
   const uint32_t rem = CG_TOTAL - sumf;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     if (lane * 4 + j == besti) { f[j] += rem; fl += rem; }
-  uint32_t run = dpp_incl_scan<false>(fl) - fl;
+  uint32_t run = cg_dpp_incl_scan<false>(fl) - fl;
   uint16_t o[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {

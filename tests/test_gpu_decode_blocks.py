@@ -42,3 +42,21 @@ def test_symbols_outside_the_searched_blocks(bin_, n_layers, n_channels, n_token
     assert_same("decoded fp16", g["out_from_oracle_payload"], want)
     assert_same("decoded own payload", g["out"],
                 oracle.decode(g["words"], g["offsets"], g["scales"], shape, cl, ca, cd))
+
+
+# Few waves: one, two and four decoding waves per workgroup (by pairs and by units), a grid that
+# is not a multiple of the XCDs, and the chunks of one cache decoded alone
+@pytest.mark.parametrize("n_ctx,n_layers,n_channels,n_tokens,chunk_len,levels", [
+    (5, 3, 130, 90, 45, (1.0, 2.0)),        # 180 waves, one per workgroup
+    (4, 32, 64, 82, 41, (1.0,)),            # 512 waves: two pairs of a unit per workgroup
+    (19, 13, 72, 44, 44, (1.0, 2.0, 4.0, 8.0)),   # 988 waves: four units of one pair
+    (1, 16, 2048, 43, 43, (1.0,)),          # 1024 waves of one pair: four units
+])
+def test_at_most_a_wave_per_simd(n_ctx, n_layers, n_channels, n_tokens, chunk_len, levels):
+    w = W.small(name=f"few_{n_ctx}_{n_layers}_{n_channels}", n_ctx=n_ctx, n_layers=n_layers,
+                n_channels=n_channels, n_tokens=n_tokens, chunk_len=chunk_len, level_mult=levels)
+    kv = W.generate(w)
+    g = run_gpu(w, kv)
+    want = oracle.decode(g["words"], g["offsets"], g["scales"], oracle.shape_from(w),
+                         w.chunk_levels(), g["ca"], g["cd"])
+    assert_same("decoded fp16", g["out"], want)
