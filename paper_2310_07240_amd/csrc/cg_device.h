@@ -265,6 +265,65 @@ struct TokEncWorkspace {
   int nbj;            // 64-token blocks per (context, chunk, layer, K/V)
 };
 TokEncWorkspace cg_encode_tokens_ws_layout(const KParams& P);
+// Launch geometry of the token layout's coders. A workgroup is w waves: w consecutive 64-token
+// blocks of one (context, chunk, layer, K/V), which share the staged tables (up to eight; while
+// the chip is far from full, under four waves per SIMD, more waves than blocks, which only help
+// to stage). per / last: workgroups of a (layer, K/V) in a whole chunk and in the last one.
+// lds: dynamic LDS that makes a workgroup of static_lds bytes so large that no CU takes more than
+// its share of a grid of up to four per CU (512 workgroups of eight waves, two per CU: without
+// it some CUs took three and others one, and a decode took 0.97 ms instead of 0.74).
+struct TokGrid {
+  int w, per, last;
+  int64_t grid;
+  size_t lds;
+};
+inline TokGrid cg_tok_grid(const KParams& P, int nbj, const size_t (&static_lds)[4]) {
+  TokGrid t;
+  const int64_t rows = (int64_t)P.B * P.NC * 2 * P.L;
+  t.w = 1;
+  int lg = 0;
+  while (t.w < 8 && (t.w < nbj || rows * 2 * t.w <= 4096)) {
+    t.w *= 2;
+    ++lg;
+  }
+  const int nb_last = (int)(((int64_t)P.T - (int64_t)(P.NC - 1) * P.CL + 63) / 64);
+  t.per = (nbj + t.w - 1) / t.w;
+  t.last = (nb_last + t.w - 1) / t.w;
+  t.grid = (int64_t)P.B * 2 * P.L * ((int64_t)(P.NC - 1) * t.per + t.last);
+  const int64_t share = (t.grid + 255) / 256;
+  t.lds = 0;
+  if (share <= 4) {
+    // just over 160 KB / (share + 1) each
+    const size_t want = (size_t)160 * 1024 / (size_t)(share + 1) + 256;
+    if (want > static_lds[lg] && want <= 64 * 1024) t.lds = want - static_lds[lg];
+  }
+  return t;
+}
+// Threads of the token layout's row kernels (tok_quantize_kernel, tok_dequant_kernel): 16 (octets)
+// or 64 channels across, times the chunk's groups, whole waves, at most 512.
+inline int cg_tok_row_threads(const KParams& P, bool vec) {
+  const int64_t n = P.CL < P.T ? P.CL : P.T;
+  const int64_t t = (n + P.G - 1) / P.G * (vec ? 16 : 64);
+  return t >= 512 ? 512 : (int)((t + 63) / 64 * 64);
+}
+// Block of the grid -> its (context, chunk, layer, K/V) and its first 64-token block.
+__device__ __forceinline__ TokGroup cg_tok_block(const KParams& P, int w, int per, int last,
+                                                 int64_t blk) {
+  TokGroup g;
+  const int64_t whole = (int64_t)(P.NC - 1) * 2 * P.L * per;   // of a context's whole chunks
+  const int64_t ctx = whole + 2 * P.L * last;
+  g.b = (int)(blk / ctx);
+  int64_t r = blk - g.b * ctx;
+  const bool tail = r >= whole;
+  if (tail) r -= whole;
+  const int n = tail ? last : per;
+  const int64_t q = r / n;
+  g.jb = (int)(r - q * n) * w;
+  g.c = tail ? P.NC - 1 : (int)(q / (2 * P.L));
+  g.lk = (int)(q % (2 * P.L));
+  g.n = P.CL < P.T - g.c * P.CL ? P.CL : P.T - g.c * P.CL;
+  return g;
+}
 hipError_t cg_launch_encode_tokens(const KParams& P, const uint16_t* kv,
                                    const uint8_t* chunk_level, const uint16_t* cdf_anchor,
                                    const uint16_t* cdf_delta, uint32_t* words, uint64_t* offsets,
