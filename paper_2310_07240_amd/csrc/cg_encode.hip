@@ -37,7 +37,8 @@ constexpr int kEncMaxUnits = 16;   // (layer, K/V, channel block) units per work
 // waves per CU leave (at 12, three waves per SIMD, each may hold 168)
 constexpr int kEncWinWaves = 12;
 constexpr int kEncStageBatch = 8;  // table-staging loads in flight per lane
-constexpr int kCompactRows = 128;  // slot rows per pass of the compaction
+constexpr int kEncHelpWaves = 8;   // waves per workgroup where some only stage tables
+constexpr int kCompactRows = 128;  // slot rows of the compaction's tile (32 per wave)
 // static LDS of the kernel with several units (masks, level maps, SIMD ids, remaining counts);
 // the dynamic LDS budget leaves 1 KB for it
 static_assert(4 * kEncMaxUnits + 4 * kEncMaxUnits * CG_MAX_LEVELS + 2 * kEncMaxUnits + kEncMaxWaves +
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(kWin ? 64 * kEncWinWaves : 1024) void encode_kernel
     KParams P, const uint16_t* __restrict__ kv, const uint8_t* __restrict__ chunk_level,
     const uint16_t* __restrict__ cdfA, const uint16_t* __restrict__ cdfD,
     uint32_t* __restrict__ slots, uint32_t slot_words, uint32_t* __restrict__ lens,
-    float* __restrict__ scales, uint32_t* __restrict__ wflags, int nw, int nu, int nsets_lds,
+    float* __restrict__ scales, uint8_t* __restrict__ wflags, int nw, int nu, int nsets_lds,
     int ustride, int scales_given) {
   // workgroup = nu units (layer, K/V, 64-channel block) x nw (context, chunk) pairs; wave w
   // codes pair slot w / nu of unit w % nu (one workgroup per CU where the grid allows, so the
@@ -271,14 +272,14 @@ __global__ __launch_bounds__(kWin ? 64 * kEncWinWaves : 1024) void encode_kernel
   int ublk, grp;
   cg_xcd_map((n_units + nu - 1) / nu, n_groups, ublk, grp);
   if (ublk * nu >= n_units) {   // past the last unit block (uniform over the workgroup)
-    if (threadIdx.x == 0) wflags[blockIdx.x] = 0u;
+    if (threadIdx.x == 0) wflags[blockIdx.x] = 0;
     return;
   }
   const int unit = ublk * nu + u;
   const int cb = unit % P.nblk;
   const int k = (unit / P.nblk) & 1, l = (unit / P.nblk) >> 1;
   const int pair = __builtin_amdgcn_readfirstlane(grp * nw + j);
-  const bool active = unit < n_units && pair < n_pairs;
+  const bool active = unit < n_units && j < nw && pair < n_pairs;
   // pairs chunk-major: the waves of a workgroup code the same chunk of consecutive contexts
   const int b = active ? pair % P.B : 0;
   const int c = active ? pair / P.B : 0;
@@ -721,7 +722,7 @@ __global__ __launch_bounds__(kWin ? 64 * kEncWinWaves : 1024) void encode_kernel
   // unit's region at once: every wave takes part in every round's staging and barriers, and
   // codes in its set's round)
   __syncthreads();
-  if (threadIdx.x == 0) wflags[blockIdx.x] = s_bad;   // every workgroup writes its flag
+  if (threadIdx.x == 0) wflags[blockIdx.x] = (uint8_t)s_bad;   // every workgroup writes its flag
   int nrounds = 1;
   if constexpr (kWin) {
     for (int uu = 0; uu < nu; ++uu) nrounds = max(nrounds, (int)s_nrounds[uu]);
@@ -785,7 +786,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_reduce(const uint32_t* __re
 // no clearing is needed between calls).
 __global__ __launch_bounds__(kScanThreads) void scan_top(uint64_t* __restrict__ partial,
                                                          int64_t nb,
-                                                         const uint32_t* __restrict__ wflags,
+                                                         const uint8_t* __restrict__ wflags,
                                                          int64_t n_wg,
                                                          uint32_t* __restrict__ status) {
   __shared__ uint64_t sh[kScanThreads / 64];
@@ -842,6 +843,74 @@ __global__ __launch_bounds__(kScanThreads) void scan_finish(const uint32_t* __re
     run += v[i];
     if (idx == S - 1) offsets[S] = run;
   }
+}
+
+// The whole scan in one workgroup, for a few thousand streams: tiles of 4096 word counts (four
+// per thread) in order, the status word as scan_top's. Three launches took 13.5 us for the 1024
+// streams of a short context, this 4.7.
+constexpr int kScanOne = 16384;   // streams
+__global__ __launch_bounds__(1024) void scan_one(const uint32_t* __restrict__ lens, int S,
+                                                 uint64_t* __restrict__ offsets,
+                                                 const uint8_t* __restrict__ wflags, int64_t n_wg,
+                                                 uint32_t* __restrict__ status) {
+  __shared__ uint32_t sh[2][16];
+  if (status) {
+    uint32_t bad = 0u;
+    for (int64_t i = threadIdx.x; i < n_wg; i += 1024) bad |= wflags[i];
+    bad = __syncthreads_or(bad != 0u);
+    if (threadIdx.x == 0) *status = bad ? 1u : 0u;
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint64_t carry = 0;
+  for (int base = 0, buf = 0; base < S; base += 4096, buf ^= 1) {
+    const int i0 = base + 4 * (int)threadIdx.x;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 + 4 <= S) {
+      v = *reinterpret_cast<const uint4*>(lens + i0);
+    } else {
+      if (i0 < S) v.x = lens[i0];
+      if (i0 + 1 < S) v.y = lens[i0 + 1];
+      if (i0 + 2 < S) v.z = lens[i0 + 2];
+    }
+    // a tile's total stays far below 2^32 (a stream's words fit its slot)
+    const uint32_t own = v.x + v.y + v.z + v.w;
+    const uint32_t incl = cg_dpp_incl_scan<false>(own);
+    if ((threadIdx.x & 63) == 63) sh[buf][wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) before += sh[buf][w];
+      total += sh[buf][w];
+    }
+    uint64_t run = carry + before + incl - own;
+    const uint32_t e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (i0 + q < S) offsets[i0 + q] = run;
+      run += e[q];
+      if (i0 + q == S - 1) offsets[S] = run;
+    }
+    carry += total;
+  }
+}
+
+// offsets [S + 1] from the streams' word counts; status as scan_top's.
+hipError_t launch_scan(const uint32_t* lens, int64_t S, uint64_t* partial, uint64_t* offsets,
+                       const uint8_t* wflags, int64_t n_wg, uint32_t* status, uint32_t slot_words,
+                       hipStream_t st) {
+  if (S <= kScanOne && slot_words < (1u << 19)) {
+    hipLaunchKernelGGL(scan_one, dim3(1), dim3(1024), 0, st, lens, (int)S, offsets, wflags, n_wg,
+                       status);
+    return hipGetLastError();
+  }
+  const int64_t nb = (S + kScanBlock - 1) / kScanBlock;
+  hipLaunchKernelGGL(scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, st, lens, S, partial);
+  hipLaunchKernelGGL(scan_top, dim3(1), dim3(kScanThreads), 0, st, partial, nb, wflags, n_wg,
+                     status);
+  hipLaunchKernelGGL(scan_finish, dim3((unsigned)nb), dim3(kScanThreads), 0, st, lens, S, partial,
+                     offsets);
+  return hipGetLastError();
 }
 
 // ---- token-parallel layout (Sec. 6: the paper's decoder runs one thread per token) -----------
@@ -1126,33 +1195,71 @@ __global__ __launch_bounds__(256) void compact_kernel(KParams P, const uint32_t*
   __syncthreads();
   const uint32_t K = s_max;
   const uint32_t* src = slots + (uint64_t)grp * slot_words * 64;
-  // kCompactRows words of every stream per pass (kCompactRows / 4 chunk rows of 1 KB, a wave
-  // reading whole rows): every thread has eight 16-byte loads in flight
-  for (uint32_t k0 = 0; k0 < K; k0 += kCompactRows) {
-    uint4 v[8];
+  // A wave moves blocks of 32 words of every stream (8 chunk rows of 1 KB, its loads in flight
+  // together, those of its next block during the writes of this one), wave w blocks w, w + 4, ...,
+  // through its own part of the tile, so the waves wait for nothing but their own loads (128
+  // words per pass of the workgroup between barriers: 859 us for a Llama-2-7B-shaped 8K cache
+  // and 80 for a Mistral-7B-shaped 4K one; now 860, about 3 TB/s, and 77). Groups of up to 32
+  // words are one block, whose streams the four waves share.
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  uint32_t (*const tile)[65] = ctile + 32 * wave;
+  const int half = lane >> 5, kr = lane & 31;
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // 32 consecutive words of streams L and L + 1 at a time
+  auto write = [&](int L0, uint32_t k0) __attribute__((always_inline)) {
+    const int L = L0 + half;
+    if (k0 + kr < s_len[L]) words[s_off[L] + k0 + kr] = tile[kr][L];
+  };
+  if (K <= 32u) {
+    const int col = 16 * wave + (lane & 15);
+    u32x4 v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t m = (lane >> 4) + 4 * i;
+      v[i] = 4 * m < K ? *reinterpret_cast<const u32x4*>(src + ((uint64_t)m * 64 + col) * 4)
+                       : u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int m = 4 * ((lane >> 4) + 4 * i);
+      tile[m + 0][col] = v[i].x;
+      tile[m + 1][col] = v[i].y;
+      tile[m + 2][col] = v[i].z;
+      tile[m + 3][col] = v[i].w;
+    }
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) write(16 * wave + i, 0u);
+    return;
+  }
+  u32x4 v[8];
+  auto load = [&](uint32_t k0) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const uint32_t cr = (t >> 6) + 4 * i;   // chunk row of this pass: words 4 cr .. 4 cr + 3
-      const uint32_t m = (k0 >> 2) + cr;      // chunk index in the slots
-      v[i] = 4 * m < K ? *reinterpret_cast<const uint4*>(src + ((uint64_t)m * 64 + (t & 63)) * 4)
-                       : make_uint4(0u, 0u, 0u, 0u);
+      const uint32_t m = min((k0 >> 2) + i, (K - 1) >> 2);   // chunk row (past the last: the last)
+      v[i] = *reinterpret_cast<const u32x4*>(src + ((uint64_t)m * 64 + lane) * 4);
     }
+  };
+  uint32_t k0 = 32u * wave;
+  if (k0 < K) load(k0);
+  for (; k0 < K; k0 += 128u) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int cr = (t >> 6) + 4 * i;
-      ctile[4 * cr + 0][t & 63] = v[i].x;
-      ctile[4 * cr + 1][t & 63] = v[i].y;
-      ctile[4 * cr + 2][t & 63] = v[i].z;
-      ctile[4 * cr + 3][t & 63] = v[i].w;
+      tile[4 * i + 0][lane] = v[i].x;
+      tile[4 * i + 1][lane] = v[i].y;
+      tile[4 * i + 2][lane] = v[i].z;
+      tile[4 * i + 3][lane] = v[i].w;
     }
-    __syncthreads();
-#pragma unroll
-    for (int pass = 0; pass < 32; ++pass) {   // 16 lanes write 16 consecutive words of a stream
-      const int L = (pass & 3) * 16 + (t >> 4);
-      const uint32_t kr = (pass >> 2) * 16 + (t & 15), k = k0 + kr;
-      if (k < s_len[L]) words[s_off[L] + k] = ctile[kr][L];
-    }
-    __syncthreads();
+    wave_sync();
+    if (k0 + 128u < K) load(k0 + 128u);
+#pragma unroll 8
+    for (int i = 0; i < 64; i += 2) write(i, k0);
+    wave_sync();
   }
 }
 
@@ -1166,10 +1273,11 @@ struct EncGeom {
   int64_t n_groups, g1;
   size_t lds;
   bool win;      // delta tables staged as windows (encode_kernel<kG, true>)
+  int helpers = 0;   // waves past the nw nu that code: they only stage tables
   int ustride;   // u16 per unit region
 };
 
-EncGeom enc_geometry(const KParams& P) {
+EncGeom enc_geometry(const KParams& P, bool spread = true) {
   EncGeom g;
   const int64_t n_pairs = (int64_t)P.B * P.NC;
   int nw = (int)(n_pairs < kEncMaxWaves ? n_pairs : kEncMaxWaves);
@@ -1211,14 +1319,40 @@ EncGeom enc_geometry(const KParams& P) {
     g.ustride = g.nsets * 64 * kEncTabStride;
     g.lds = lds_for(nw, nu);
   }
-  g.g1 = cg_xcd_grid((n_units + g.nu - 1) / g.nu, n_groups);
+  // Few waves in workgroups of more than four (several on a SIMD while other CUs have none): the
+  // smallest workgroups that make one round on 256 CUs instead, as the decoder's (240 waves of
+  // 1536 tokens in 40 workgroups of six: 607 us, now 385). Short chunks are left: their time is
+  // the staging of tables, which the pairs of a unit share. And up to one wave per SIMD, helpers
+  // stage the tables (16 waves of 256 tokens: 67 us, now 61).
+  const bool few = spread && n_units * n_pairs <= 4 * 256;
+  if (few && g.nw * g.nu > 4 && (n_pairs == 1 || (P.CL < P.T ? P.CL : P.T) >= 40)) {
+    for (int waves = 1; waves <= 4; ++waves) {
+      int w1 = 0;
+      for (int w = 1; w <= waves && w <= n_pairs; ++w)
+        if (waves % w == 0 && lds_for(w, waves / w) <= kEncLdsBudget &&
+            (n_units + waves / w - 1) / (waves / w) * ((n_pairs + w - 1) / w) <= 256)
+          w1 = w;   // the last fit: more pairs of a unit share its tables
+      if (!w1) continue;
+      g.nw = w1;
+      g.nu = waves / w1;
+      g.nsets = w1 < P.NLV ? w1 : P.NLV;
+      g.n_groups = (n_pairs + w1 - 1) / w1;
+      g.win = false;
+      g.ustride = g.nsets * 64 * kEncTabStride;
+      g.lds = lds_for(w1, g.nu);
+      break;
+    }
+  }
+  if (few && !g.win && g.nw * g.nu < kEncHelpWaves)
+    g.helpers = kEncHelpWaves / g.nu * g.nu - g.nw * g.nu;
+  g.g1 = cg_xcd_grid((n_units + g.nu - 1) / g.nu, g.n_groups);
   return g;
 }
 
 }  // namespace
 
 // Workspace: the status word (offset 0, read by cg_get_status), the encode workgroups'
-// non-finite flags, one worst-case slot per lane of every (row, 64-channel block) wave (lanes
+// non-finite flags (a byte each), one worst-case slot per lane of every (row, 64-channel block) wave (lanes
 // past C included), per-stream word counts, and the scan's block totals.
 EncWorkspace cg_encode_ws_layout(const KParams& P, uint32_t slot_words) {
   EncWorkspace w;
@@ -1227,7 +1361,9 @@ EncWorkspace cg_encode_ws_layout(const KParams& P, uint32_t slot_words) {
   const uint64_t slot_lanes = (uint64_t)P.B * P.NC * P.L * 2 * P.nblk * 64;
   w.status_off = 0;
   w.wflags_off = 256;
-  w.slots_off = align256(w.wflags_off + (uint64_t)enc_geometry(P).g1 * 4ull);
+  // (four bytes for each workgroup of the grid without the spreading of few waves, at least 256:
+  // enough for either grid)
+  w.slots_off = align256(w.wflags_off + (uint64_t)enc_geometry(P, false).g1 * 4ull);
   w.lens_off = align256(w.slots_off + slot_lanes * slot_words * 4ull);
   w.partial_off = align256(w.lens_off + (uint64_t)S * 4ull);
   w.total = align256(w.partial_off + (uint64_t)(nb > 0 ? nb : 1) * 8ull);
@@ -1243,7 +1379,7 @@ hipError_t cg_launch_encode(const KParams& P, const uint16_t* kv, const uint8_t*
   uint8_t* base = static_cast<uint8_t*>(ws);
   uint32_t* status =
       status_out ? status_out : reinterpret_cast<uint32_t*>(base + lay.status_off);
-  uint32_t* wflags = reinterpret_cast<uint32_t*>(base + lay.wflags_off);
+  uint8_t* wflags = base + lay.wflags_off;
   uint32_t* slots = reinterpret_cast<uint32_t*>(base + lay.slots_off);
   uint32_t* lens = reinterpret_cast<uint32_t*>(base + lay.lens_off);
   uint64_t* partial = reinterpret_cast<uint64_t*>(base + lay.partial_off);
@@ -1256,7 +1392,8 @@ hipError_t cg_launch_encode(const KParams& P, const uint16_t* kv, const uint8_t*
   hipError_t e =
       hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds);
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)g.g1), block(64 * g.nw * g.nu);
+  // (the shared absmax of own scales takes no helpers)
+  const dim3 grid((unsigned)g.g1), block(64 * (g.nw * g.nu + (scales_given ? g.helpers : 0)));
 #define CG_ENCODE_LAUNCH(KG, KW)                                                              \
   hipLaunchKernelGGL((encode_kernel<KG, KW>), grid, block, g.lds, st, P, kv, chunk_level,     \
                      cdf_anchor, cdf_delta, slots, slot_words, lens, scales, wflags, g.nw,    \
@@ -1271,13 +1408,8 @@ hipError_t cg_launch_encode(const KParams& P, const uint16_t* kv, const uint8_t*
 #undef CG_ENCODE_LAUNCH
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t nb = (P.S + kScanBlock - 1) / kScanBlock;
-  hipLaunchKernelGGL(scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, st, lens, P.S,
-                     partial);
-  hipLaunchKernelGGL(scan_top, dim3(1), dim3(kScanThreads), 0, st, partial, nb,
-                     (const uint32_t*)wflags, g.g1, status);
-  hipLaunchKernelGGL(scan_finish, dim3((unsigned)nb), dim3(kScanThreads), 0, st, lens, P.S,
-                     partial, offsets);
+  e = launch_scan(lens, P.S, partial, offsets, wflags, g.g1, status, slot_words, st);
+  if (e != hipSuccess) return e;
   const int64_t groups = (int64_t)P.B * P.NC * P.L * 2 * P.nblk;
   hipLaunchKernelGGL(compact_kernel<false>, dim3((unsigned)groups), dim3(256), 0, st, P, slots,
                      slot_words, lens, offsets, 0, words);
@@ -1344,13 +1476,8 @@ hipError_t cg_launch_encode_tokens(const KParams& P, const uint16_t* kv,
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t St = cg_token_streams(P);
-  const int64_t nb = (St + kScanBlock - 1) / kScanBlock;
-  hipLaunchKernelGGL(scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, st, lens, St,
-                     partial);
-  hipLaunchKernelGGL(scan_top, dim3(1), dim3(kScanThreads), 0, st, partial, nb,
-                     (const uint32_t*)nullptr, (int64_t)0, (uint32_t*)nullptr);
-  hipLaunchKernelGGL(scan_finish, dim3((unsigned)nb), dim3(kScanThreads), 0, st, lens, St,
-                     partial, offsets);
+  e = launch_scan(lens, St, partial, offsets, nullptr, 0, nullptr, slot_words, st);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(compact_kernel<true>, dim3((unsigned)lay.n_groups), dim3(256), 0, st, P,
                      slots, slot_words, lens, offsets, lay.nbj, words);
   return hipGetLastError();
