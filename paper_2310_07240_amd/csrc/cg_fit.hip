@@ -14,7 +14,7 @@
 // takes two neighbouring channels (one dword per token) over half of the wave's groups; the
 // slice is read once, into registers, with all its loads in flight together, and both passes
 // work from the registers. Otherwise the rows are read once per pass, a lane per channel.
-// fit_pass_kernel (whole 64-channel blocks) and fit_levels_kernel (any channel count) fit the
+// fit_pass_kernel (an even channel count) and fit_levels_kernel (any channel count) fit the
 // anchors and several levels from one quantization with 16-bit counts; fit_hold_kernel is
 // fit_pass_kernel's one-level case at G = 10 with the slice held in registers between its
 // maxima and its count (the cache read once) and resident workgroups that walk the blocks.
@@ -423,7 +423,7 @@ constexpr int kHistP = 255;      // 255 symbols, no padding (odd, so rows fall o
 constexpr int kHoldGroups = 5;   // fit_hold_kernel: groups of a slice held (1536-token chunks: 5)
 constexpr int kBufWord3 = 0x00020000;   // raw buffer descriptor: 32-bit data format
 
-// fit_pass_kernel: whole 64-channel blocks. A lane takes a channel pair cp (one dword per
+// fit_pass_kernel: an even channel count. A lane takes a channel pair cp (one dword per
 // token) over one of 32 slices of each chunk's groups (slice = 2 wave + lane / 32). The slice is
 // read twice: first for the magnitude maximum (combined over the slices in LDS into the chunk's
 // scale), then group by group from the last one back, so that the rows read last, the likeliest
@@ -567,11 +567,12 @@ __global__ __launch_bounds__(kFitThreads, kNl == 1 ? 8 : 4) void fit_pass_kernel
     }
     __syncthreads();
     const uint32_t b0 = sm[2 * cp] & 0xFFFFu, b1 = sm[2 * cp + 1] & 0xFFFFu;
-    bad |= (b0 >= 0x7C00u) | (b1 >= 0x7C00u);
+    const bool in = cb * 64 + 2 * cp < P.C;   // else: past the last channel, nothing is kept
+    bad |= in & ((b0 >= 0x7C00u) | (b1 >= 0x7C00u));
     const float m0 = cg_h2f((uint16_t)b0), m1 = cg_h2f((uint16_t)b1);
     const float sc0 = (m0 == 0.0f) ? 1.0f : m0 / 127.0f;
     const float sc1 = (m1 == 0.0f) ? 1.0f : m1 / 127.0f;
-    if (scales && with_anchor && wave == 0 && lane < 32) {   // every wave holds the maxima
+    if (scales && with_anchor && wave == 0 && lane < 32 && in) {   // every wave holds the maxima
       put_scale(scales, P, pr / P.NC, pr % P.NC, l, k, cb * 64 + 2 * cp, sc0);
       put_scale(scales, P, pr / P.NC, pr % P.NC, l, k, cb * 64 + 2 * cp + 1, sc1);
     }
@@ -685,6 +686,7 @@ __global__ __launch_bounds__(kFitThreads, kNl == 1 ? 8 : 4) void fit_pass_kernel
   for (int tb = wave; tb < nk * 64; tb += kFitWaves) {
     const int kind = tb >> 6, cl = tb & 63;
     const int chx = cb * 64 + cl;
+    if (chx >= P.C) continue;
     uint16_t* dst = (with_anchor && kind == 0)
                         ? cdf_anchor + ((int64_t)lk * P.C + chx) * 256
                         : cdf_delta + (((int64_t)(lv0 + kind - with_anchor) * P.L * 2 + lk) * P.C +
@@ -693,7 +695,7 @@ __global__ __launch_bounds__(kFitThreads, kNl == 1 ? 8 : 4) void fit_pass_kernel
   }
 }
 
-// fit_hold_kernel: one level, G = 10, whole 64-channel blocks, at most kH groups per slice (the
+// fit_hold_kernel: one level, G = 10, an even channel count, at most kH groups per slice (the
 // paper's 1536-token chunks: 5). The lanes and slices of fit_pass_kernel, but a slice stays in
 // registers from its maxima to its count, so the cache is read once: as each group is counted,
 // its registers take the same rows of the next slice, whose maxima are taken one group later.
@@ -777,11 +779,12 @@ __global__ __launch_bounds__(kFitThreads, 4) void fit_hold_kernel(
     atomicMax(&sm[2 * cp + 1], tag | m.y);
     __syncthreads();
     const uint32_t b0 = sm[2 * cp] & 0xFFFFu, b1 = sm[2 * cp + 1] & 0xFFFFu;
-    bad |= (b0 >= 0x7C00u) | (b1 >= 0x7C00u);
+    const bool in = cb * 64 + 2 * cp < P.C;   // else: past the last channel, nothing is kept
+    bad |= in & ((b0 >= 0x7C00u) | (b1 >= 0x7C00u));
     const float m0 = cg_h2f((uint16_t)b0), m1 = cg_h2f((uint16_t)b1);
     const float sc0 = (m0 == 0.0f) ? 1.0f : m0 / 127.0f;
     const float sc1 = (m1 == 0.0f) ? 1.0f : m1 / 127.0f;
-    if (scales && with_anchor && wave == 0 && lane < 32) {
+    if (scales && with_anchor && wave == 0 && lane < 32 && in) {
       put_scale(scales, P, pr / P.NC, pr % P.NC, l, k, cb * 64 + 2 * cp, sc0);
       put_scale(scales, P, pr / P.NC, pr % P.NC, l, k, cb * 64 + 2 * cp + 1, sc1);
     }
@@ -837,6 +840,7 @@ __global__ __launch_bounds__(kFitThreads, 4) void fit_hold_kernel(
       for (int tb = wave; tb < nk * 64; tb += kFitWaves) {
         const int kind = tb >> 6, cl = tb & 63;
         const int chx = cb * 64 + cl;
+        if (chx >= P.C) continue;
         uint16_t* dst = (with_anchor && kind == 0)
                             ? cdf_anchor + ((int64_t)lk * P.C + chx) * 256
                             : cdf_delta + (((int64_t)(lv0 + kind - with_anchor) * P.L * 2 + lk) *
@@ -1094,12 +1098,22 @@ hipError_t launch_fit_pass(const KParams& P, const uint16_t* kv, int lv0, int nl
   }
 }
 
-// fit_pass_kernel's conditions: whole 64-channel blocks, and byte offsets inside one (context,
-// layer, K/V) slab, plus the reads past the last token (a slice's: under 1/32 of a chunk and a
-// group; the one-level maxima pass's: under 128 rows), that stay below 2^31
-bool fit_pass_applies(const KParams& P) {
-  return P.C % 64 == 0 && (int64_t)P.T * P.C * 2 < ((int64_t)1 << 30) &&
-         (int64_t)(P.T + 128) * P.C * 2 < ((int64_t)1 << 31);
+// The conditions of fit_pass_kernel and fit_hold_kernel. Byte offsets inside one (context, layer,
+// K/V) slab, plus the reads past the last token (a slice's: under 1/32 of a chunk and a group; the
+// one-level maxima pass's: under 128 rows), stay below 2^31. Whole 64-channel blocks, or an even
+// channel count and dword-aligned rows: a lane's two channels are then one dword of every row, and
+// those past the last channel read on into the next row (or zero past the slab) and are not
+// kept. The 16-byte maxima of one level's fit_pass_kernel take whole octets of channels.
+// (Ragged blocks with a lane per channel and a load per value: 159 us for 5 layers of 3 x 2003
+// tokens x 200 channels at two levels, now 85; 40 layers of 4000 x 160 at one: 146, now 52.)
+bool fit_pass_applies(const KParams& P, const uint16_t* kv) {
+  if (!((int64_t)P.T * P.C * 2 < ((int64_t)1 << 30) &&
+        (int64_t)(P.T + 128) * P.C * 2 < ((int64_t)1 << 31)))
+    return false;
+  if (P.C % 64 == 0) return true;
+  if (P.C % 2 != 0 || (reinterpret_cast<uintptr_t>(kv) & 3) != 0) return false;
+  const bool one_level_pass = P.NLV % (kPassKinds - 1) == 1;
+  return P.C % 8 == 0 || !one_level_pass || P.G != 10 || fit_hold_grid(P) != 0;
 }
 }  // namespace
 
@@ -1131,7 +1145,7 @@ hipError_t cg_launch_fit_levels(const KParams& P, const uint16_t* kv, uint16_t* 
                   : hipSuccess;
   }
   if (status) hipLaunchKernelGGL(zero_word, dim3(1), dim3(64), 0, st, status);
-  const bool pass = fit_pass_applies(P);
+  const bool pass = fit_pass_applies(P, kv);
   if (P.NLV == 1 && !pass)   // one level, any channel count: the 32-bit kernel of cg_fit_cdf
     return fit_slice_in_registers(P)
                ? launch_fit_kernel<false, true>(P, kv, 0, cdf_anchor, cdf_delta, nullptr, st,

@@ -1,0 +1,48 @@
+"""The fit of channel counts that are not whole 64-channel blocks: even ones take the kernels that
+read two channels as a dword, odd ones and rows off a dword the others. Tables and scales against
+the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2310_07240_amd import workloads as W
+from gpu_helpers import assert_same, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+L5 = (1.0, 2.0, 4.0, 8.0, 16.0)
+
+
+@pytest.mark.parametrize("channels,tokens,chunk,levels,group,offset", [
+    (2, 33, 20, (1.0,), 10, 0),             # one dword per row, the slab's end inside a block
+    (66, 95, 40, (1.0, 2.0), 10, 0),
+    (70, 61, 61, L5, 10, 0),                # four levels and one more
+    (72, 1700, 1700, (1.0,), 10, 0),        # chunks too long to hold: the 16-byte maxima
+    (74, 1700, 1700, (1.0,), 10, 0),        # and those of rows without whole octets
+    (70, 1650, 1650, L5, 10, 0),
+    (130, 200, 90, (1.0, 4.0, 8.0), 7, 0),
+    (66, 95, 40, (1.0,), 10, 1),            # rows off a dword
+    (66, 95, 40, (1.0, 2.0), 10, 3),
+    (65, 95, 40, (1.0, 2.0), 10, 0),
+])
+def test_ragged_fit(channels, tokens, chunk, levels, group, offset):
+    torch = torch_cuda()
+    from paper_2310_07240_amd.cachegen import Codec, CodecParams
+    w = W.small(name="fit", n_ctx=2, n_layers=2, n_tokens=tokens, n_channels=channels,
+                chunk_len=chunk, level_mult=levels, group_size=group)
+    kv_np = W.generate(w)
+    ca, cd = oracle.fit_all_levels(kv_np, oracle.shape_from(w))
+    codec = Codec(CodecParams.of(w))
+    n = kv_np.size
+    kv = torch.empty(n + 8, dtype=torch.int16, device="cuda")
+    kv.fill_(0x7C00)                         # +Inf around the cache: never part of a result
+    kv = kv[offset:offset + n].view(kv_np.shape)
+    kv.copy_(torch.from_numpy(kv_np.view(np.int16)))
+    scales = torch.empty((codec.n_streams,), dtype=torch.float32, device="cuda")
+    status = torch.empty((1,), dtype=torch.int32, device="cuda")
+    ga, gd = codec.fit(kv, status=status, scales=scales)
+    assert_same("cdf_anchor", ga.cpu().numpy().view(np.uint16), ca)
+    assert_same("cdf_delta", gd.cpu().numpy().view(np.uint16), cd)
+    assert int(status[0]) == 0
+    _, _, osc = oracle.encode(kv_np, oracle.shape_from(w), w.chunk_levels(), ca, cd)
+    assert_same("scales", scales.cpu().numpy(), osc)
