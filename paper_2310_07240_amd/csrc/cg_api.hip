@@ -35,8 +35,13 @@ int make_kparams(const cg_params* p, KParams* K) {
   K->L = p->n_layers;
   K->T = p->n_tokens;
   K->C = p->n_channels;
-  K->G = p->group_size;
   K->CL = p->chunk_len;
+  // A group longer than every chunk is the chunk: the kernels get at most the longest chunk's
+  // length, so that a group count rounded up (n + G - 1) and a slice's end (slices x G) stay
+  // within 32 bits for group sizes up to 2^31 - 1. (At least 11: 10 selects kernels of its own.)
+  const int32_t longest = p->chunk_len < p->n_tokens ? p->chunk_len : p->n_tokens;
+  const int32_t most = longest > 11 ? longest : 11;
+  K->G = p->group_size < most ? p->group_size : most;
   K->NC = (int32_t)(((int64_t)p->n_tokens + p->chunk_len - 1) / p->chunk_len);
   K->NLV = p->n_levels;
   K->nblk = (p->n_channels + 63) / 64;
