@@ -1763,7 +1763,7 @@ __global__ __launch_bounds__(512) void tok_dequant_kernel(KParams P, const uint8
                                                           const uint8_t* __restrict__ chunk_level,
                                                           uint16_t* __restrict__ out) {
   constexpr int kO = kV == 8 ? 16 : 64;   // threads across channels
-  const int kR = (int)blockDim.x / kO;    // and across groups (cg_tok_row_threads)
+  const int kR = (int)blockDim.x / kO;    // and across groups (cg_tok_row_grid)
   const int nb = (P.C + kO * kV - 1) / (kO * kV);
   const int cb = (int)(blockIdx.x % nb);
   int64_t r = blockIdx.x / nb;
@@ -1854,12 +1854,11 @@ hipError_t cg_launch_decode_tokens(const KParams& P, const uint32_t* words,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t rows = (int64_t)P.B * P.NC * 2 * P.L;
   const bool vec = P.C % 8 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-  const unsigned grid = (unsigned)(rows * (vec ? (P.C + 127) / 128 : (P.C + 63) / 64));
+  const TokRowGrid rg = cg_tok_row_grid(P, vec);
   const auto dequant = vec ? (P.G == 10 ? &tok_dequant_kernel<8, 10> : &tok_dequant_kernel<8, 0>)
                            : (P.G == 10 ? &tok_dequant_kernel<1, 10> : &tok_dequant_kernel<1, 0>);
-  hipLaunchKernelGGL(dequant, dim3(grid), dim3(cg_tok_row_threads(P, vec)), 0, st, P, sym, scales,
+  hipLaunchKernelGGL(dequant, dim3((unsigned)rg.grid), dim3(rg.threads), 0, st, P, sym, scales,
                      chunk_level, out);
   return hipGetLastError();
 }

@@ -277,12 +277,16 @@ struct TokGrid {
   int64_t grid;
   size_t lds;
 };
+// A launch takes fewer than 2^32 threads: where more waves per workgroup (the last workgroup of a
+// chunk partly empty) would pass that, fewer are taken.
+constexpr int64_t kMaxLaunchThreads = 0xFFFFFFFFll;
 inline TokGrid cg_tok_grid(const KParams& P, int nbj, const size_t (&static_lds)[4]) {
   TokGrid t;
   const int64_t rows = (int64_t)P.B * P.NC * 2 * P.L;
   t.w = 1;
   int lg = 0;
-  while (t.w < 8 && (t.w < nbj || rows * 2 * t.w <= 4096)) {
+  while (t.w < 8 && (t.w < nbj || rows * 2 * t.w <= 4096) &&
+         rows * ((nbj + 2 * t.w - 1) / (2 * t.w)) * (2 * t.w) * 64 <= kMaxLaunchThreads) {
     t.w *= 2;
     ++lg;
   }
@@ -299,12 +303,24 @@ inline TokGrid cg_tok_grid(const KParams& P, int nbj, const size_t (&static_lds)
   }
   return t;
 }
-// Threads of the token layout's row kernels (tok_quantize_kernel, tok_dequant_kernel): 16 (octets)
-// or 64 channels across, times the chunk's groups, whole waves, at most 512.
-inline int cg_tok_row_threads(const KParams& P, bool vec) {
+// Launch geometry of the token layout's row kernels (tok_quantize_kernel, tok_dequant_kernel). A
+// workgroup takes 128 (octets) or 64 channels of one (context, chunk, layer, K/V) in 16 or 64
+// threads across, times the chunk's groups, whole waves, at most 512, and at most what a launch of
+// that many workgroups takes.
+struct TokRowGrid {
+  int64_t grid;
+  int threads;
+};
+inline TokRowGrid cg_tok_row_grid(const KParams& P, bool vec) {
+  TokRowGrid g;
+  g.grid = (int64_t)P.B * P.NC * 2 * P.L * (vec ? (P.C + 127) / 128 : (P.C + 63) / 64);
   const int64_t n = P.CL < P.T ? P.CL : P.T;
-  const int64_t t = (n + P.G - 1) / P.G * (vec ? 16 : 64);
-  return t >= 512 ? 512 : (int)((t + 63) / 64 * 64);
+  int64_t t = ((n + P.G - 1) / P.G * (vec ? 16 : 64) + 63) / 64 * 64;
+  if (t > 512) t = 512;
+  const int64_t most = kMaxLaunchThreads / g.grid / 64 * 64;
+  if (t > most) t = most;
+  g.threads = t < 64 ? 64 : (int)t;
+  return g;
 }
 // Block of the grid -> its (context, chunk, layer, K/V) and its first 64-token block.
 __device__ __forceinline__ TokGroup cg_tok_block(const KParams& P, int w, int per, int last,

@@ -933,7 +933,7 @@ __global__ __launch_bounds__(512) void tok_quantize_kernel(KParams P, const uint
                                                            float* __restrict__ scales) {
   constexpr int kO = kV == 8 ? 16 : 64;             // threads across channels
   constexpr int kMaxR = 512 / kO;
-  const int kR = (int)blockDim.x / kO;              // and across groups (cg_tok_row_threads)
+  const int kR = (int)blockDim.x / kO;              // and across groups (cg_tok_row_grid)
   typedef _Float16 half8 __attribute__((ext_vector_type(8)));
   __shared__ __attribute__((aligned(16))) _Float16 part[kMaxR][kO * kV];
   const int nb = (P.C + kO * kV - 1) / (kO * kV);
@@ -1450,12 +1450,12 @@ hipError_t cg_launch_encode_tokens(const KParams& P, const uint16_t* kv,
   uint32_t* lens = reinterpret_cast<uint32_t*>(base + lay.lens_off);
   uint64_t* partial = reinterpret_cast<uint64_t*>(base + lay.partial_off);
   const uint32_t slot_words = cg_token_slot_words(P);
-  const int64_t rows = (int64_t)P.B * P.NC * 2 * P.L;
   const bool vec = P.C % 8 == 0 && (reinterpret_cast<uintptr_t>(kv) & 15) == 0;
+  const TokRowGrid rg = cg_tok_row_grid(P, vec);
   const auto quantize = vec ? (P.G == 10 ? &tok_quantize_kernel<8, 10> : &tok_quantize_kernel<8, 0>)
                             : (P.G == 10 ? &tok_quantize_kernel<1, 10> : &tok_quantize_kernel<1, 0>);
-  hipLaunchKernelGGL(quantize, dim3((unsigned)(rows * (vec ? (P.C + 127) / 128 : (P.C + 63) / 64))),
-                     dim3(cg_tok_row_threads(P, vec)), 0, st, P, kv, chunk_level, sym, scales);
+  hipLaunchKernelGGL(quantize, dim3((unsigned)rg.grid), dim3(rg.threads), 0, st, P, kv, chunk_level,
+                     sym, scales);
   const auto tok_lds = [](int w) {
     return kEncTile * 2 * kEncTokTab * sizeof(uint16_t) + w * kRing * 64 * sizeof(uint32_t);
   };
