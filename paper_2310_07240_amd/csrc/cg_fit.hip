@@ -1098,6 +1098,32 @@ hipError_t launch_fit_pass(const KParams& P, const uint16_t* kv, int lv0, int nl
   }
 }
 
+// Whether ragged blocks (not 64 channels) of chunks of up to ng groups go to fit_pass_kernel and
+// fit_hold_kernel rather than to fit_levels_kernel or, with one level, fit_kernel. Those give each
+// of 16 waves its own groups, a lane one channel; here a chunk's groups fill 32 slices, a lane counts
+// two channels of a group one after the other. With more than 16 groups more waves have work here
+// (8 layers of 3072 tokens x 200 channels, 1536-token chunks, 17 groups of 91 tokens: 142 us there
+// and 101 here at two levels, 256 and 135 at four); with fewer half of the slices are empty, and it
+// depends on the passes, of three levels after the anchors there and of four here, and the longer
+// the group the more the second channel costs. 4 x 8 layers x 200 channels, there and here:
+//   one level    6 groups of 64 tokens 99.7 and 97.5 us; 12 of 128 164 and 174
+//   two levels   6 groups of 64 111 and 121; one of 1536 792 and 1176 (as above)
+//   four levels  4 groups of 400 905 and 754; 3 of 500 1084 and 927
+//   six levels   6 groups of 64 219 and 263
+//   eight levels 4 groups of 400 1561 and 1458; 3 of 500 1835 and 1805; one of 64 239 and 282
+// At G = 10 a group's rows are loaded together here, and only the shortest chunks at a number of
+// levels that takes as many passes here lose (2 groups, five levels: 81 and 87; two levels 50 and
+// 50; 16 groups, five levels 90 and 84).
+bool fit_ragged_pass(const KParams& P) {
+  const int64_t n = P.CL < P.T ? P.CL : P.T;
+  const int64_t ng = (n + P.G - 1) / P.G;
+  const bool fewer = P.NLV % (kPassKinds - 1) == 0;   // a pass fewer than there
+  if (P.G == 10) return ng > 4 || P.NLV <= 2 || fewer;
+  if (ng > kFitWaves) return true;
+  if (ng <= 2 && P.G > 16) return false;
+  return P.NLV == 1 ? P.G <= 64 : fewer;
+}
+
 // The conditions of fit_pass_kernel and fit_hold_kernel. Byte offsets inside one (context, layer,
 // K/V) slab, plus the reads past the last token (a slice's: under 1/32 of a chunk and a group; the
 // one-level maxima pass's: under 128 rows), stay below 2^31. Whole 64-channel blocks, or an even
@@ -1112,6 +1138,7 @@ bool fit_pass_applies(const KParams& P, const uint16_t* kv) {
     return false;
   if (P.C % 64 == 0) return true;
   if (P.C % 2 != 0 || (reinterpret_cast<uintptr_t>(kv) & 3) != 0) return false;
+  if (!fit_ragged_pass(P)) return false;
   const bool one_level_pass = P.NLV % (kPassKinds - 1) == 1;
   return P.C % 8 == 0 || !one_level_pass || P.G != 10 || fit_hold_grid(P) != 0;
 }

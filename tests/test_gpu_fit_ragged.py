@@ -24,6 +24,15 @@ L5 = (1.0, 2.0, 4.0, 8.0, 16.0)
     (66, 95, 40, (1.0,), 10, 1),            # rows off a dword
     (66, 95, 40, (1.0, 2.0), 10, 3),
     (65, 95, 40, (1.0, 2.0), 10, 0),
+    # either side of the rule that leaves few groups per chunk to the kernels of one channel a lane
+    (66, 272, 272, (1.0, 2.0), 17, 0),
+    (66, 273, 273, (1.0, 2.0), 17, 0),      # 17 groups, the last of one token
+    (66, 150, 150, (1.0,), 64, 0),
+    (66, 150, 150, (1.0,), 65, 0),
+    (70, 40, 40, (1.0, 2.0, 4.0), 10, 0),
+    (70, 41, 41, (1.0, 2.0, 4.0), 10, 0),
+    (66, 51, 51, L5[:4], 17, 0),            # three groups and two
+    (66, 34, 34, L5[:4], 17, 0),
 ])
 def test_ragged_fit(channels, tokens, chunk, levels, group, offset):
     torch = torch_cuda()
