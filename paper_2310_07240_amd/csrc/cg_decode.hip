@@ -1854,7 +1854,7 @@ hipError_t cg_launch_decode_tokens(const KParams& P, const uint32_t* words,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool vec = P.C % 8 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  const bool vec = cg_tok_octets(P, out);
   const TokRowGrid rg = cg_tok_row_grid(P, vec);
   const auto dequant = vec ? (P.G == 10 ? &tok_dequant_kernel<8, 10> : &tok_dequant_kernel<8, 0>)
                            : (P.G == 10 ? &tok_dequant_kernel<1, 10> : &tok_dequant_kernel<1, 0>);

@@ -303,6 +303,19 @@ inline TokGrid cg_tok_grid(const KParams& P, int nbj, const size_t (&static_lds)
   }
   return t;
 }
+// Whether the token layout's row kernels take eight channels a thread (p: the fp16 cache they read or
+// write): rows of whole 16-byte octets, unless a chunk has few long groups. A group is one thread's,
+// so then few threads of a wave work and each codes eight channels of every row one after the other;
+// with a channel a thread the groups' chains are an eighth as long. Encode / decode of 8 layers x
+// 72 channels, with octets and without: 2 chunks of 1536 tokens as one group each 723 / 464 and
+// 351 / 356 us; 2 contexts of 8 groups of 300 204 / 160 and 171 / 135, of 10 groups 202 / 167 and
+// 259 / 200; 3 of 12 groups of 150 144 / 110 and 173 / 133; 16 of one group of 64 71 / 55 and 56 / 58.
+inline bool cg_tok_octets(const KParams& P, const void* p) {
+  if (P.C % 8 != 0 || (reinterpret_cast<uintptr_t>(p) & 15) != 0) return false;
+  const int64_t n = P.CL < P.T ? P.CL : P.T;
+  const int64_t ng = (n + P.G - 1) / P.G;
+  return ng == 1 ? n < 64 || P.G == 10 : ng > 8 || P.G <= 200;
+}
 // Launch geometry of the token layout's row kernels (tok_quantize_kernel, tok_dequant_kernel). A
 // workgroup takes 128 (octets) or 64 channels of one (context, chunk, layer, K/V) in 16 or 64
 // threads across, times the chunk's groups, whole waves, at most 512, and at most what a launch of

@@ -1450,7 +1450,7 @@ hipError_t cg_launch_encode_tokens(const KParams& P, const uint16_t* kv,
   uint32_t* lens = reinterpret_cast<uint32_t*>(base + lay.lens_off);
   uint64_t* partial = reinterpret_cast<uint64_t*>(base + lay.partial_off);
   const uint32_t slot_words = cg_token_slot_words(P);
-  const bool vec = P.C % 8 == 0 && (reinterpret_cast<uintptr_t>(kv) & 15) == 0;
+  const bool vec = cg_tok_octets(P, kv);
   const TokRowGrid rg = cg_tok_row_grid(P, vec);
   const auto quantize = vec ? (P.G == 10 ? &tok_quantize_kernel<8, 10> : &tok_quantize_kernel<8, 0>)
                             : (P.G == 10 ? &tok_quantize_kernel<1, 10> : &tok_quantize_kernel<1, 0>);

@@ -24,6 +24,15 @@ CASES = [
     W.small(name="w8_c200", n_layers=1, n_tokens=64, chunk_len=64, n_channels=200),
     W.small(name="w8_c129_g64", n_layers=1, n_tokens=129, chunk_len=129, n_channels=129,
             group_size=64),
+    # octets of channels with few long groups a chunk: a channel a thread, and either side of it
+    W.small(name="one_group_64", n_layers=1, n_tokens=64, chunk_len=64, n_channels=72, group_size=64),
+    W.small(name="one_group_63", n_layers=1, n_tokens=63, chunk_len=63, n_channels=72, group_size=64),
+    W.small(name="groups8_201", n_layers=1, n_tokens=1700, chunk_len=1600, n_channels=24,
+            group_size=201),
+    W.small(name="groups9_201", n_layers=1, n_tokens=1700, chunk_len=1609, n_channels=24,
+            group_size=201),
+    W.small(name="groups2_200", n_layers=1, n_tokens=400, chunk_len=400, n_channels=24,
+            group_size=200),
 ]
 
 
