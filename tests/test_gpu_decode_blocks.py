@@ -51,6 +51,8 @@ def test_symbols_outside_the_searched_blocks(bin_, n_layers, n_channels, n_token
     (4, 32, 64, 82, 41, (1.0,)),            # 512 waves: two pairs of a unit per workgroup
     (19, 13, 72, 44, 44, (1.0, 2.0, 4.0, 8.0)),   # 988 waves: four units of one pair
     (1, 16, 2048, 43, 43, (1.0,)),          # 1024 waves of one pair: four units
+    (6, 4, 72, 25, 12, (1.0, 4.0)),         # chunks of 12 tokens and one
+    (16, 32, 64, 11, 11, (1.0,)),           # 1024 waves: four pairs of a unit
 ])
 def test_at_most_a_wave_per_simd(n_ctx, n_layers, n_channels, n_tokens, chunk_len, levels):
     w = W.small(name=f"few_{n_ctx}_{n_layers}_{n_channels}", n_ctx=n_ctx, n_layers=n_layers,
