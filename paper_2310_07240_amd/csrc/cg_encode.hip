@@ -1343,7 +1343,10 @@ EncGeom enc_geometry(const KParams& P, bool spread = true) {
       break;
     }
   }
-  if (few && !g.win && g.nw * g.nu < kEncHelpWaves)
+  // (not where one batch of loads of the coding waves, 16 tables each, stages all of a workgroup's
+  // 64 nu nsets tables: the helpers then only add to the barriers; four contexts x 16 layers x 256
+  // channels of 39 and 100 tokens 51.4 and 64.6 us with them, 50.2 and 62.7 without)
+  if (few && !g.win && g.nw * g.nu < kEncHelpWaves && g.nw < 4 * g.nsets)
     g.helpers = kEncHelpWaves / g.nu * g.nu - g.nw * g.nu;
   g.g1 = cg_xcd_grid((n_units + g.nu - 1) / g.nu, g.n_groups);
   return g;
