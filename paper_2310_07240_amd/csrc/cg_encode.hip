@@ -38,7 +38,7 @@ constexpr int kEncMaxUnits = 16;   // (layer, K/V, channel block) units per work
 constexpr int kEncWinWaves = 12;
 constexpr int kEncStageBatch = 8;  // table-staging loads in flight per lane
 constexpr int kEncHelpWaves = 8;   // waves per workgroup where some only stage tables
-constexpr int kCompactRows = 128;  // slot rows of the compaction's tile (32 per wave)
+constexpr int kCompactRows = 128;  // slot rows of the compaction's tile
 // static LDS of the kernel with several units (masks, level maps, SIMD ids, remaining counts);
 // the dynamic LDS budget leaves 1 KB for it
 static_assert(4 * kEncMaxUnits + 4 * kEncMaxUnits * CG_MAX_LEVELS + 2 * kEncMaxUnits + kEncMaxWaves +
@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(64 * kW) void tok_encode_kernel(
 // consecutive words per stream. Channel layout (kTok false): group = (row, 64-channel block),
 // streams row * C + block * 64 + i. Token layout: group = (context, chunk, layer and K/V,
 // 64-token block), streams tok_stream(...) of the block's tokens.
-template <bool kTok>
+template <bool kTok, bool kOwn>
 __global__ __launch_bounds__(256) void compact_kernel(KParams P, const uint32_t* __restrict__ slots,
                                                       uint32_t slot_words,
                                                       const uint32_t* __restrict__ lens,
@@ -1195,14 +1195,42 @@ __global__ __launch_bounds__(256) void compact_kernel(KParams P, const uint32_t*
   __syncthreads();
   const uint32_t K = s_max;
   const uint32_t* src = slots + (uint64_t)grp * slot_words * 64;
-  // A wave moves blocks of 32 words of every stream (8 chunk rows of 1 KB, its loads in flight
-  // together, those of its next block during the writes of this one), wave w blocks w, w + 4, ...,
-  // through its own part of the tile, so the waves wait for nothing but their own loads (128
-  // words per pass of the workgroup between barriers: 859 us for a Llama-2-7B-shaped 8K cache
-  // and 80 for a Mistral-7B-shaped 4K one; now 860, about 3 TB/s, and 77). Groups of up to 32
-  // words are one block, whose streams the four waves share.
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  if constexpr (!kOwn) {
+    // kCompactRows words of every stream per pass (kCompactRows / 4 chunk rows of 1 KB, a wave
+    // reading whole rows): every thread has eight 16-byte loads in flight
+    for (uint32_t k0 = 0; k0 < K; k0 += kCompactRows) {
+      u32x4 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t m = (k0 >> 2) + wave + 4 * i;   // chunk row
+        v[i] = 4 * m < K ? *reinterpret_cast<const u32x4*>(src + ((uint64_t)m * 64 + lane) * 4)
+                         : u32x4{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int m = 4 * (wave + 4 * i);
+        ctile[m + 0][lane] = v[i].x;
+        ctile[m + 1][lane] = v[i].y;
+        ctile[m + 2][lane] = v[i].z;
+        ctile[m + 3][lane] = v[i].w;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int pass = 0; pass < 32; ++pass) {   // 16 lanes write 16 consecutive words of a stream
+        const int L = (pass & 3) * 16 + (t >> 4);
+        const uint32_t kr = (pass >> 2) * 16 + (t & 15), k = k0 + kr;
+        if (k < s_len[L]) words[s_off[L] + k] = ctile[kr][L];
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  // kOwn: a wave moves blocks of 32 words of every stream (8 chunk rows of 1 KB, its loads in flight
+  // together, those of its next block during the writes of this one), wave w blocks w, w + 4, ...,
+  // through its own part of the tile, so the waves wait for nothing but their own loads. Groups
+  // of up to 32 words are one block, whose streams the four waves share.
   uint32_t (*const tile)[65] = ctile + 32 * wave;
   const int half = lane >> 5, kr = lane & 31;
   auto wave_sync = [] {
@@ -1261,6 +1289,21 @@ __global__ __launch_bounds__(256) void compact_kernel(KParams P, const uint32_t*
     for (int i = 0; i < 64; i += 2) write(i, k0);
     wave_sync();
   }
+}
+
+// Whether the compaction's waves take blocks of their own (kOwn), by the symbols of a stream (tokens
+// of a chunk, or channels) and the launch's groups. One block of 32 words per stream: always (96
+// layers x 1024 channels of 40 tokens 14.7 us in passes and 13.0 so, 2 x 256 of 100 tokens 4.8 and
+// 4.3). More: where the groups fill the CUs and the blocks, of about 5 bits a symbol, at least three
+// quarters of the waves' rounds (1536-token chunks, eight blocks: 1024 groups 32.4 and 29.1, 28160
+// 645 and 623, but 256 13.5 and 14.2; 256 tokens, two blocks: 3072 groups 22.6 and 24.4). Token
+// streams differ in length (an anchor token's symbols take 7 to 8 bits) and stay with the passes
+// (256 channels, 4608 groups: 32.1 and 35.8; 1024: 82 and 86).
+bool compact_own(const KParams& P, bool tok, int64_t groups) {
+  if (tok) return P.C <= 128;
+  const int64_t n = P.CL < P.T ? P.CL : P.T;
+  const int64_t nb = (n * 5 + 1023) / 1024;
+  return nb <= 1 || (groups >= 1024 && nb >= (nb + 3) / 4 * 3);
 }
 
 inline uint64_t align256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
@@ -1414,8 +1457,10 @@ hipError_t cg_launch_encode(const KParams& P, const uint16_t* kv, const uint8_t*
   e = launch_scan(lens, P.S, partial, offsets, wflags, g.g1, status, slot_words, st);
   if (e != hipSuccess) return e;
   const int64_t groups = (int64_t)P.B * P.NC * P.L * 2 * P.nblk;
-  hipLaunchKernelGGL(compact_kernel<false>, dim3((unsigned)groups), dim3(256), 0, st, P, slots,
-                     slot_words, lens, offsets, 0, words);
+  const auto compact = compact_own(P, false, groups) ? &compact_kernel<false, true>
+                                                     : &compact_kernel<false, false>;
+  hipLaunchKernelGGL(compact, dim3((unsigned)groups), dim3(256), 0, st, P, slots, slot_words, lens,
+                     offsets, 0, words);
   return hipGetLastError();
 }
 
@@ -1481,7 +1526,9 @@ hipError_t cg_launch_encode_tokens(const KParams& P, const uint16_t* kv,
   const int64_t St = cg_token_streams(P);
   e = launch_scan(lens, St, partial, offsets, nullptr, 0, nullptr, slot_words, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(compact_kernel<true>, dim3((unsigned)lay.n_groups), dim3(256), 0, st, P,
-                     slots, slot_words, lens, offsets, lay.nbj, words);
+  const auto compact = compact_own(P, true, lay.n_groups) ? &compact_kernel<true, true>
+                                                          : &compact_kernel<true, false>;
+  hipLaunchKernelGGL(compact, dim3((unsigned)lay.n_groups), dim3(256), 0, st, P, slots, slot_words,
+                     lens, offsets, lay.nbj, words);
   return hipGetLastError();
 }
