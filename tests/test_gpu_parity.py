@@ -251,6 +251,7 @@ def test_windowed_tables_chunk_ranges():
         assert np.all(part[..., mask, :] == 0)
 
 
+LEVELS8 = (1.0, 2.0, 4.0, 8.0, 16.0, 32.0, 64.0, 128.0)
 FIT_CASES = [
     W.MISTRAL_7B_4K.with_(name="fit_mistral_l3", n_layers=3, layer_bin=(0.5, 1.0, 1.5)),
     W.small(name="fit_levels4_regs", n_layers=2, n_channels=128, n_tokens=1600, chunk_len=1536,
@@ -279,6 +280,12 @@ FIT_CASES = [
     # per CU): some workgroups take two items, the next item's first slice loaded across
     W.small(name="fit_level1_items270", n_layers=3, n_channels=2880, n_tokens=300, chunk_len=128,
             level_mult=(1.0,)),
+    # odd channel counts, a lane per channel: three, four, five and eight levels (the anchors and
+    # three levels in the first pass, up to four in each further one), G = 10 and 7, two contexts
+    *(W.small(name=f"fit_levels{len(m)}_g{g}_c{c}", n_ctx=2, n_layers=2, n_channels=c, n_tokens=150,
+              chunk_len=64, group_size=g, level_mult=m)
+      for c, g, m in ((65, 10, (1.0, 2.0, 4.0)), (71, 7, (1.0, 2.0, 4.0, 8.0)),
+                      (65, 10, (1.0, 1.5, 2.0, 3.0, 5.0)), (71, 10, LEVELS8), (65, 7, LEVELS8))),
     # more than 2^16 deltas of one channel: the 32-bit per-level path
     W.small(name="fit_long_t76000", n_layers=1, n_channels=64, n_tokens=76000, chunk_len=1536,
             level_mult=(1.0, 4.0)),
@@ -314,9 +321,15 @@ def test_fit_all_levels_equals_oracle_and_per_level(w):
 SCALE_CASES = [
     FIT_CASES[0],   # one level, 64-channel blocks
     W.small(name="scales_one_level_c70", n_tokens=37, chunk_len=1536, level_mult=(1.0,),
-            random_levels=False),   # one level, ragged channels: the 32-bit fit kernel
+            random_levels=False),   # one level, an even channel count: the one-read kernel
+    W.small(name="scales_one_level_c71", n_tokens=37, chunk_len=1536, level_mult=(1.0,),
+            random_levels=False),   # an odd one: the 32-bit kernel
     W.small(name="scales_levels8_c70", n_layers=2, n_channels=70, n_tokens=300, chunk_len=64,
-            level_mult=(1.0, 2.0, 4.0, 8.0, 16.0, 32.0, 64.0, 128.0)),   # a lane per channel
+            level_mult=LEVELS8),    # a lane per two channels, two passes of four levels
+    W.small(name="scales_levels8_c71", n_layers=2, n_channels=71, n_tokens=300, chunk_len=64,
+            level_mult=LEVELS8),    # a lane per channel, three passes
+    W.small(name="scales_levels4_c65_g7", n_layers=2, n_channels=65, n_tokens=100, chunk_len=40,
+            group_size=7, level_mult=LEVELS8[:4]),
     COMPACT[0],     # windowed delta tables in the encoder, coop absmax path in cg_encode
     FIT_CASES[-1],  # more than 2^16 deltas per channel: the per-level 32-bit path
 ]
