@@ -135,25 +135,6 @@ __device__ __forceinline__ uint32_t delta_leaf(const uint16_t* q, uint32_t ti, u
   return c;
 }
 
-// 16 j - 127 for the largest j in [0, 15] with v[j] <= ti (sorted v, v[0] <= ti < v[16]): a
-// binary search by selects on registers, each decision also picking the candidates of the
-// later levels (a chain of four compare / select steps), its index scaled and biased so that
-// adding the offset of the symbol inside the block gives the quantized value.
-__device__ __forceinline__ int fence_q(const uint32_t (&v)[17], uint32_t ti) {
-  const bool c3 = v[8] <= ti;
-  const uint32_t p4 = c3 ? v[12] : v[4];
-  const uint32_t p2a = c3 ? v[10] : v[2], p2b = c3 ? v[14] : v[6];
-  const uint32_t p1a = c3 ? v[9] : v[1], p1b = c3 ? v[11] : v[3];
-  const uint32_t p1c = c3 ? v[13] : v[5], p1d = c3 ? v[15] : v[7];
-  const bool c2 = p4 <= ti;
-  const uint32_t p2 = c2 ? p2b : p2a;
-  const uint32_t p1e = c2 ? p1c : p1a, p1f = c2 ? p1d : p1b;
-  const bool c1 = p2 <= ti;
-  const uint32_t p1 = c1 ? p1f : p1e;
-  const bool c0 = p1 <= ti;
-  return (c3 ? 1 : -127) + (c2 ? 64 : 0) + (c1 ? 32 : 0) + (c0 ? 16 : 0);
-}
-
 __global__ __launch_bounds__(1024) void decode_kernel(
     KParams P, const uint32_t* __restrict__ words, const uint64_t* __restrict__ offsets,
     const float* __restrict__ scales, const uint8_t* __restrict__ chunk_level,
@@ -897,33 +878,41 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   return pa;
 }
 
+// Largest i in [0, 15] with entry i <= ti of 16 sorted ones (entry 0 is), entries 2 k and 2 k + 1
+// in the halves of dword k of a (k < 4) and b: a bit at a time, `one` times the index. pl is the
+// dword holding entry i, and pn the next one (e8: the dword after the last), b1 its low bit.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t find16(const u32x4& a, const u32x4& b, uint32_t e8, uint32_t ti,
+                                           uint32_t one, uint32_t& pl, uint32_t& pn, bool& b1) {
+  const bool b8 = (b.x & 0xFFFFu) <= ti;
+  const uint32_t x4 = b8 ? b.z : a.z;
+  const bool b4 = (x4 & 0xFFFFu) <= ti;
+  const uint32_t xa = b8 ? b.y : a.y, xb = b8 ? b.w : a.w;
+  const uint32_t x2 = b4 ? xb : xa;
+  const bool b2 = (x2 & 0xFFFFu) <= ti;
+  const uint32_t y = b4 ? x4 : (b8 ? b.x : a.x);
+  const uint32_t z = b4 ? (b8 ? e8 : b.x) : x4;
+  pl = b2 ? x2 : y;
+  pn = b2 ? z : x2;
+  b1 = (pl >> 16) <= ti;
+  return (b8 ? 8u * one : 0u) + (b4 ? 4u * one : 0u) + (b2 ? 2u * one : 0u) + (b1 ? one : 0u);
+}
+
 // The same for a table in the piece layout, where the chain of one symbol is what counts (a SIMD
 // runs one wave, see cg_launch_decode): the block's 16 entries and the one after them come
 // in one LDS round trip, and the search and the candidate's bounds are selects on registers (one
 // round trip per symbol instead of three, for about eight more instructions). Returns the symbol.
 __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)[16],
                                                const PieceTab& T) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) const u32x4 lds_cu32x4;
   const uint32_t th = g10_target(st), ti = th >> 16;
   const uint32_t qa = g10_block(fT, th, T.tb, PieceTab::kS);
-  // entries 2 k and 2 k + 1 of the block in the halves of e[k], entry 16 in e8
   const u32x4 e03 = *(lds_cu32x4*)(uintptr_t)qa, e47 = *(lds_cu32x4*)(uintptr_t)(qa + 1024u);
   const uint32_t e8 = lds_ld16(qa + 2048u);
-  // the largest i with entry i <= ti (entry 0 is), a bit at a time; x4, x2: the dwords of the
-  // entries compared, pl: the dword holding entry i, pn: the next one
-  const bool b8 = (e47.x & 0xFFFFu) <= ti;
-  const uint32_t x4 = b8 ? e47.z : e03.z;
-  const bool b4 = (x4 & 0xFFFFu) <= ti;
-  const uint32_t xa = b8 ? e47.y : e03.y, xb = b8 ? e47.w : e03.w;
-  const uint32_t x2 = b4 ? xb : xa;
-  const bool b2 = (x2 & 0xFFFFu) <= ti;
-  const uint32_t y = b4 ? x4 : (b8 ? e47.x : e03.x);
-  const uint32_t z = b4 ? (b8 ? e8 : e47.x) : x4;
-  const uint32_t pl = b2 ? x2 : y, pn = b2 ? z : x2;
-  const bool b1 = (pl >> 16) <= ti;
+  uint32_t pl, pn;
+  bool b1;
+  const uint32_t i = find16(e03, e47, e8, ti, 1u, pl, pn, b1);
   const uint32_t pair = __builtin_amdgcn_alignbit(pn, pl, b1 ? 16u : 0u);
-  const uint32_t i = (b8 ? 8u : 0u) + (b4 ? 4u : 0u) + (b2 ? 2u : 0u) + (b1 ? 1u : 0u);
   uint32_t sym = ((qa - T.tb) >> 7) + i;
   const uint32_t D = st.D, R = st.R;
   uint32_t lo_off = __umulhi(R, pair << 16);
@@ -1580,26 +1569,6 @@ struct TokTab {
   }
 };
 
-// Largest i in [0, 15] with entry i <= ti of 16 sorted ones (entry 0 is), entries 2 k and 2 k + 1
-// in the halves of dword k of a (k < 4) and b: a bit at a time, `one` times the index. pl is the
-// dword holding entry i, and pn the next one (e8: the dword after the last), b1 its low bit.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint32_t find16(const u32x4& a, const u32x4& b, uint32_t e8, uint32_t ti,
-                                           uint32_t one, uint32_t& pl, uint32_t& pn, bool& b1) {
-  const bool b8 = (b.x & 0xFFFFu) <= ti;
-  const uint32_t x4 = b8 ? b.z : a.z;
-  const bool b4 = (x4 & 0xFFFFu) <= ti;
-  const uint32_t xa = b8 ? b.y : a.y, xb = b8 ? b.w : a.w;
-  const uint32_t x2 = b4 ? xb : xa;
-  const bool b2 = (x2 & 0xFFFFu) <= ti;
-  const uint32_t y = b4 ? x4 : (b8 ? b.x : a.x);
-  const uint32_t z = b4 ? (b8 ? e8 : b.x) : x4;
-  pl = b2 ? x2 : y;
-  pn = b2 ? z : x2;
-  b1 = (pl >> 16) <= ti;
-  return (b8 ? 8u * one : 0u) + (b4 ? 4u * one : 0u) + (b2 ? 2u * one : 0u) + (b1 ? one : 0u);
-}
-
 // One symbol of a token stream under the staged table T.
 __device__ __forceinline__ uint32_t tok_symbol(G10Lane& st, const TokTab& T) {
   typedef __attribute__((address_space(3))) const u32x4 lds_cu32x4;
@@ -1891,8 +1860,7 @@ hipError_t cg_launch_decode(const KParams& P, const uint32_t* words, const uint6
            (n_units + nu) / (nu + 1) * n_groups >= 256)
       ++nu;
     const int msets = nw < P.NLV ? nw : P.NLV;
-    // With several levels, the delta tables can instead be staged as windows (decode_g10_kernel
-    // <true>): a unit then needs a region of one table set (its anchor tables) plus window
+    // With several levels, the delta tables can instead be staged as windows (Stage::kWindows): a unit then needs a region of one table set (its anchor tables) plus window
     // descriptors, so more units fit a workgroup. Used when that allows more units.
     const size_t rows = (size_t)nw * kG10 * 64 * sizeof(uint16_t);   // per unit
     const size_t set_bytes = (size_t)64 * kTabStride * sizeof(uint16_t);
