@@ -699,18 +699,22 @@ __device__ __forceinline__ void g10_fences_win(uint32_t (&fT)[kF], const WinTab&
 // it the latency of its dependent LDS reads). The expected
 // cost follows from the tables: `out` is the probability mass outside the blocks, in 2^-16,
 // less the 1 that every symbol's frequency holds whether it occurs or not, summed over the wave
-// (a step of the wave leaves the straight path if any of its lanes does).
-// The kernel is bound by VALU issue (0.96 busy with 70.7 instructions per symbol step on a
-// Mistral-7B-shaped 4K cache); the narrow searches and the high-word products (g10_symbol) took
-// that to 62.7 and the decode from 544 to 518 us there (the deltas of its shallowest third still
-// need all 16 blocks), and from 5770 to 5270 us on a Llama-2-70B-shaped 16K cache with four
-// levels. kOutCost as 110 and 60 (narrow searches for wider tables): 530 and 559 us, 5260 and
-// 5290 us.
+// (a step of the wave leaves the straight path if any of its lanes does). Tables fitted over
+// several contexts may hold the mass outside for one of them alone, whose wave the others wait
+// for, so the cost counts once per context. With 16 blocks and so: Mistral-7B-shaped 4K cache 547
+// and 534 us (the deltas of its shallowest third still need all 16), 80 layers x 8192 tokens at
+// four levels 2998 and 2725, 3 contexts x 20 layers x 2000 tokens x 640 channels 531 and 508.
+// kOutCost as 60 and 110 (narrow searches for wider tables) on the first: 580 and 551 us where
+// 250 took 540.
+// Not for several contexts in workgroups of 16 waves: four waves per SIMD hide each other's
+// latency, and what counts is the slowest wave of each round (16 contexts x 32 layers x 256 channels of
+// 600 and 1000 tokens: 341 and 540 us with 16 blocks, 347 and 580 so; one context in 16 waves, 40
+// layers x 2048 tokens x 5120 channels: 3094 and 3011).
 constexpr uint32_t kOutCost = 250;
 // fewest tokens of a chunk for which the choice pays (it takes about a microsecond)
 constexpr int kNarrowMin = 256;
 template <class Tab>
-__device__ __forceinline__ int g10_blocks(const Tab& T, int& k0) {
+__device__ __forceinline__ int g10_blocks(const Tab& T, int n_ctx, int& k0) {
   const int med = g10_find(T, 32768u);
   auto out = [&](int W) __attribute__((always_inline)) {
     const int a = Tab::window(med, W), e = a + W;
@@ -719,8 +723,9 @@ __device__ __forceinline__ int g10_blocks(const Tab& T, int& k0) {
     const uint32_t sum = cg_dpp_incl_scan<false>((lo & 0xFFFFu) + (hi & 0xFFFFu));
     return (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
   };
-  const uint32_t c8 = (8u << 16), c4 = (12u << 16);   // instructions saved, times 2^16
-  const uint32_t o8 = out(128) * kOutCost, o4 = out(64) * kOutCost;
+  const uint64_t cost = (uint64_t)kOutCost * (uint32_t)n_ctx;
+  const uint64_t c8 = (8u << 16), c4 = (12u << 16);   // instructions saved, times 2^16
+  const uint64_t o8 = out(128) * cost, o4 = out(64) * cost;
   int kf = 16;
   if (o8 < c8) kf = 8;
   if (o4 < c4 && (kf == 16 || c4 - o4 > c8 - o8)) kf = 4;
@@ -866,7 +871,10 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   uint32_t hoff = __umulhi(R, st.c1);
   uint32_t d = D - lo_off;
   uint32_t rsz = hoff - lo_off;
-  if (d >= rsz) {
+  // (a wave-uniform test first: the walk then lies outside the loop. As a plain branch its 1.2 KB sat
+  // between any two symbols, with a jump over it for each: Mistral-7B-shaped 4K cache 540 us, now
+  // 529; 16 contexts x 32 layers x 600 tokens x 256 channels 356 and 349)
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(d >= rsz) != 0, 0)) if (d >= rsz) {
     const int sym = (int)((pa - tb) / kS);
     // the neighbour on D's side; the whole table's candidate where the search covered a part of
     // the table only or had no target (R = 2^32: the target is D >> 16)
@@ -919,7 +927,7 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   uint32_t hoff = __umulhi(R, pair & 0xFFFF0000u);
   uint32_t d = D - lo_off;
   uint32_t rsz = hoff - lo_off;
-  if (d >= rsz) {
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(d >= rsz) != 0, 0)) if (d >= rsz) {
     const int nxt = R == 0u ? g10_find(T, D >> 16) : T.first((int)sym, ti, D < lo_off);
     sym = (uint32_t)g10_walk(T, D, R, nxt, lo_off, hoff, d, rsz);
   }
@@ -1502,6 +1510,7 @@ __global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024)
   // the delta loop is written out per number of searched blocks, and once more, with all 16, for
   // rows that are not made of whole 16-byte octets of channels
   const bool full = (P.C & 7) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  const bool narrow = full && n >= kNarrowMin && (P.B == 1 || nw * nu < kMaxWaves);
   {
     if constexpr (kCompact) {
       const uint32_t d = desc[(u * msets + set) * 64 + lsrc];
@@ -1509,7 +1518,7 @@ __global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024)
       const WinTab T(lds_addr(tabs + u * ustride) + (d & 0xFFFFFu) - 32u * (uint32_t)g0, 16 * g0,
                      16 * (g1 + 1));
       int k0;
-      const int kf = full && n >= kNarrowMin ? g10_blocks(T, k0) : 16;
+      const int kf = narrow ? g10_blocks(T, P.B, k0) : 16;
       auto groups_of = [&](auto kF, auto kFull) __attribute__((always_inline)) {
         uint32_t fD[decltype(kF)::value];
         g10_fences_win(fD, T, g0, g1, decltype(kF)::value == 16 ? 0 : k0);
@@ -1528,7 +1537,7 @@ __global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024)
     } else {
       const ColTab T(tabs + u * ustride + set * kColSet + lsrc);
       int k0;
-      const int kf = full && n >= kNarrowMin ? g10_blocks(T, k0) : 16;
+      const int kf = narrow ? g10_blocks(T, P.B, k0) : 16;
       auto groups_of = [&](auto kF, auto kFull) __attribute__((always_inline)) {
         uint32_t fD[decltype(kF)::value];
         g10_fences(fD, T, decltype(kF)::value == 16 ? 0 : k0);
@@ -1588,7 +1597,7 @@ __device__ __forceinline__ uint32_t tok_symbol(G10Lane& st, const TokTab& T) {
   uint32_t hoff = __umulhi(R, pair & 0xFFFF0000u);
   uint32_t d = D - lo_off;
   uint32_t rsz = hoff - lo_off;
-  if (d >= rsz) {
+  if (d >= rsz) {   // (the uniform test of g10_symbol: 889 us for the 4K cache, this 874)
     const int nxt = R == 0u ? g10_find(T, D >> 16) : T.first((int)sym, ti, D < lo_off);
     sym = (uint32_t)g10_walk(T, D, R, nxt, lo_off, hoff, d, rsz);
   }

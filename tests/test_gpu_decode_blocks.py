@@ -16,7 +16,8 @@ LDS_BUDGET = 160 * 1024 - 1024   # dynamic LDS of a workgroup
 
 def decode_stage(w, n_pairs=None):
     """How a group-of-10 decode of n_pairs (context, chunk) pairs stages its delta tables, as
-    cg_launch_decode decides it: "pieces", "windows" or "columns"."""
+    cg_launch_decode decides it: "pieces", "windows" or "columns"; and the waves that decode in a
+    workgroup."""
     pairs = n_pairs or w.n_ctx * -(-w.n_tokens // w.chunk_len)
     units = 2 * w.n_layers * -(-w.n_channels // 64)
     levels = len(w.level_mult)
@@ -45,16 +46,18 @@ def decode_stage(w, n_pairs=None):
             pu = waves // pw
             if (pu * pw == waves and piece_lds(pw, pu) <= LDS_BUDGET
                     and -(-units // pu) * -(-pairs // pw) <= 256):
-                return "pieces"
+                return "pieces", waves
     if sets > 1 and nuc > nu:
-        return "windows"
-    return "pieces" if nw * nu <= 4 and piece_lds(nw, nu) <= LDS_BUDGET else "columns"
+        return "windows", nw * nuc
+    return ("pieces" if nw * nu <= 4 and piece_lds(nw, nu) <= LDS_BUDGET else "columns"), nw * nu
 
 
-def searched_blocks(w, cd, stage):
+def searched_blocks(w, cd):
     """The numbers of blocks the waves of a decode of w search, as the kernel chooses them from the
     delta tables cd [levels, L, 2, C, 256]."""
-    if stage == "pieces" or w.n_channels % 8 or min(w.chunk_len, w.n_tokens) < 256:
+    stage, waves = decode_stage(w)
+    if (stage == "pieces" or w.n_channels % 8 or min(w.chunk_len, w.n_tokens) < 256
+            or (w.n_ctx > 1 and waves == 16)):
         return {16}
     cum = cd.astype(np.int64)
     cum[..., 255] = 65536
@@ -72,7 +75,7 @@ def searched_blocks(w, cd, stage):
         pad = -w.n_channels % 64   # lanes past the last channel repeat their block's first
         mass = np.concatenate([mass, np.repeat(mass[..., w.n_channels // 64 * 64][..., None],
                                                pad, -1)], -1) if pad else mass
-        return 250 * mass.reshape(*mass.shape[:-1], -1, 64).sum(-1)
+        return 250 * w.n_ctx * mass.reshape(*mass.shape[:-1], -1, 64).sum(-1)
 
     gain8, gain4 = (8 << 16) - out(128), (12 << 16) - out(64)
     kf = np.where(gain8 > 0, 8, 16)
@@ -96,11 +99,11 @@ def foreign_payload(w, kv, ca, cd):
 
 
 def check(w, stage, blocks):
-    assert decode_stage(w) == stage
+    assert decode_stage(w)[0] == stage
     shape = oracle.shape_from(w)
     kv = W.generate(w)
     ca, cd = oracle.fit_all_levels(kv, shape)
-    assert searched_blocks(w, cd, stage) == blocks
+    assert searched_blocks(w, cd) == blocks
     payload, want = foreign_payload(w, kv, ca, cd)
     g = run_gpu(w, kv, decode_oracle_payload=payload)
     assert_same("decoded fp16", g["out_from_oracle_payload"], want)
@@ -111,15 +114,18 @@ def check(w, stage, blocks):
 
 # The layers' delta bins set the tables' widths (the narrower the bin, the wider the table), so that
 # the waves of one call search 16, 8 and 4 blocks. More than 1024 waves: whole tables at one level,
-# windows at four. Rows that are not made of whole octets of channels search 16.
+# windows at four. Rows that are not made of whole octets of channels search 16, as do several
+# contexts in workgroups of 16 waves.
 @pytest.mark.timeout(300)
-@pytest.mark.parametrize("n_channels,n_tokens,levels,stage,blocks", [
-    (728, 3840, (1.0,), "columns", {4, 8, 16}),
-    (5504, 768, (1.0, 1.5, 2.0, 4.0), "windows", {4, 8, 16}),
-    (730, 3840, (1.0,), "columns", {16}),
+@pytest.mark.parametrize("n_ctx,n_channels,n_tokens,levels,stage,blocks", [
+    (1, 728, 3840, (1.0,), "columns", {4, 8, 16}),
+    (1, 5504, 768, (1.0, 1.5, 2.0, 4.0), "windows", {4, 8, 16}),
+    (3, 728, 1280, (1.0,), "columns", {4, 8, 16}),
+    (1, 730, 3840, (1.0,), "columns", {16}),
+    (2, 728, 2048, (1.0,), "columns", {16}),
 ])
-def test_narrow_searches(n_channels, n_tokens, levels, stage, blocks):
-    check(W.small(name=f"narrow_{stage}_{n_channels}", n_layers=3, n_channels=n_channels,
+def test_narrow_searches(n_ctx, n_channels, n_tokens, levels, stage, blocks):
+    check(W.small(name=f"narrow_{stage}_{n_channels}", n_ctx=n_ctx, n_layers=3, n_channels=n_channels,
                   n_tokens=n_tokens, chunk_len=256, level_mult=levels, layer_bin=(0.05, 1.4, 3.0),
                   outlier_frac=0.0), stage, blocks)
 
@@ -155,7 +161,7 @@ def test_at_most_a_wave_per_simd(n_ctx, n_layers, n_channels, n_tokens, chunk_le
     from paper_2310_07240_amd.cachegen import Codec, CodecParams
     w = W.small(name=f"few_{n_ctx}_{n_layers}_{n_channels}", n_ctx=n_ctx, n_layers=n_layers,
                 n_channels=n_channels, n_tokens=n_tokens, chunk_len=chunk_len, level_mult=levels)
-    assert decode_stage(w) == decode_stage(w, n_ctx) == "pieces"
+    assert decode_stage(w)[0] == decode_stage(w, n_ctx)[0] == "pieces"
     kv = W.generate(w)
     g = run_gpu(w, kv)
     want = oracle.decode(g["words"], g["offsets"], g["scales"], oracle.shape_from(w),
