@@ -702,7 +702,7 @@ __global__ __launch_bounds__(kFitThreads, kNl == 1 ? 8 : 4) void fit_pass_kernel
 // The workgroups stay resident (one per CU) and take the (64-channel block, layer, K/V) items
 // in turn, so the next item's first slice loads while the finished item's tables are
 // normalised. Slice maxima meet in LDS under a tag that counts the workgroup's steps.
-template <int kH>
+template <int kH, bool kRag>
 __global__ __launch_bounds__(kFitThreads, 4) void fit_hold_kernel(
     KParams P, const uint16_t* __restrict__ kv, int lv0, int with_anchor,
     uint16_t* __restrict__ cdf_anchor, uint16_t* __restrict__ cdf_delta,
@@ -779,7 +779,8 @@ __global__ __launch_bounds__(kFitThreads, 4) void fit_hold_kernel(
     atomicMax(&sm[2 * cp + 1], tag | m.y);
     __syncthreads();
     const uint32_t b0 = sm[2 * cp] & 0xFFFFu, b1 = sm[2 * cp + 1] & 0xFFFFu;
-    const bool in = cb * 64 + 2 * cp < P.C;   // else: past the last channel, nothing is kept
+    // else: past the last channel (ragged blocks only), nothing is kept
+    const bool in = !kRag || cb * 64 + 2 * cp < P.C;
     bad |= in & ((b0 >= 0x7C00u) | (b1 >= 0x7C00u));
     const float m0 = cg_h2f((uint16_t)b0), m1 = cg_h2f((uint16_t)b1);
     const float sc0 = (m0 == 0.0f) ? 1.0f : m0 / 127.0f;
@@ -840,7 +841,7 @@ __global__ __launch_bounds__(kFitThreads, 4) void fit_hold_kernel(
       for (int tb = wave; tb < nk * 64; tb += kFitWaves) {
         const int kind = tb >> 6, cl = tb & 63;
         const int chx = cb * 64 + cl;
-        if (chx >= P.C) continue;
+        if (kRag && chx >= P.C) continue;
         uint16_t* dst = (with_anchor && kind == 0)
                             ? cdf_anchor + ((int64_t)lk * P.C + chx) * 256
                             : cdf_delta + (((int64_t)(lv0 + kind - with_anchor) * P.L * 2 + lk) *
@@ -1066,11 +1067,15 @@ hipError_t launch_fit_pass_nl(const KParams& P, const uint16_t* kv, int lv0, int
   const bool g10 = P.G == 10;
   if constexpr (kNl == 1) {
     if (const int grid = fit_hold_grid(P)) {
-      const void* fn = (const void*)fit_hold_kernel<kHoldGroups>;
-      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      // (whole blocks without the checks: 80 layers x 32 contexts of 19 tokens x 64 channels 119 us
+      // with them, 116 so)
+      const auto fn = P.C % 64 ? &fit_hold_kernel<kHoldGroups, true>
+                               : &fit_hold_kernel<kHoldGroups, false>;
+      hipError_t e = hipFuncSetAttribute((const void*)fn,
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((fit_hold_kernel<kHoldGroups>), dim3((unsigned)grid), dim3(kFitThreads),
-                         lds, st, P, kv, lv0, with_anchor, cdf_anchor, cdf_delta, status, scales);
+      hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kFitThreads), lds, st, P, kv, lv0,
+                         with_anchor, cdf_anchor, cdf_delta, status, scales);
       return hipGetLastError();
     }
   }
@@ -1111,14 +1116,25 @@ hipError_t launch_fit_pass(const KParams& P, const uint16_t* kv, int lv0, int nl
 //   four levels  4 groups of 400 905 and 754; 3 of 500 1084 and 927
 //   six levels   6 groups of 64 219 and 263
 //   eight levels 4 groups of 400 1561 and 1458; 3 of 500 1835 and 1805; one of 64 239 and 282
-// At G = 10 a group's rows are loaded together here, and only the shortest chunks at a number of
-// levels that takes as many passes here lose (2 groups, five levels: 81 and 87; two levels 50 and
-// 50; 16 groups, five levels 90 and 84).
+// At G = 10 a group's rows are loaded together here. Up to eight groups a chunk, each of the P.B P.NC
+// chunks of a block costs more here (the rows of five groups are requested whether or not they are
+// there), the tables at the end less, and where there are fewer blocks than CUs nothing hides it.
+// 2 layers x 66 channels, one level, there over here: 8 contexts of 16 to 80 tokens 1.02 to 1.10, 12
+// of 16 and 45 0.94 and 1.00, 16 of 29 and 45 0.90 and 0.95, 32 of 29, 45 and 80 0.81, 0.87 and 0.92;
+// 80 layers x 160 channels, 32 contexts of 21, 40 and 60 0.92, 0.98 and 1.03. Two levels: 0.93 to 0.96
+// for two groups, from 0.99 on for three (30 layers x 480 channels, two groups 1.00 to 1.16). Three and
+// five to seven levels: two groups 0.92, four 0.94 to 1.03, 16 1.05.
 bool fit_ragged_pass(const KParams& P) {
   const int64_t n = P.CL < P.T ? P.CL : P.T;
   const int64_t ng = (n + P.G - 1) / P.G;
   const bool fewer = P.NLV % (kPassKinds - 1) == 0;   // a pass fewer than there
-  if (P.G == 10) return ng > 4 || P.NLV <= 2 || fewer;
+  if (P.G == 10) {
+    const bool fills = (int64_t)P.L * 2 * P.nblk > 256;
+    const int64_t pairs = (int64_t)P.B * P.NC;
+    if (fewer || ng > 8) return true;
+    if (P.NLV == 1) return fills ? ng > 3 || pairs < 24 : pairs < (ng <= 3 ? 10 : ng <= 5 ? 14 : 20);
+    return P.NLV == 2 ? ng > 2 || fills : ng > 4;
+  }
   if (ng > kFitWaves) return true;
   if (ng <= 2 && P.G > 16) return false;
   return P.NLV == 1 ? P.G <= 64 : fewer;
