@@ -1292,9 +1292,9 @@ __global__ __launch_bounds__(256) void compact_kernel(KParams P, const uint32_t*
 }
 
 // Whether the compaction's waves take blocks of their own (kOwn), by the symbols of a stream (tokens
-// of a chunk, or channels) and the launch's groups. One block of 32 words per stream: always (96
-// layers x 1024 channels of 40 tokens 14.7 us in passes and 13.0 so, 2 x 256 of 100 tokens 4.8 and
-// 4.3). More: where the groups fill the CUs and the blocks, of about 5 bits a symbol, at least three
+// of a chunk, or channels) and the launch's groups. One block of 32 words per stream, of the longest
+// in each group at about 7 bits a symbol: always (2 x 48 layers x 1024 channels of 140 tokens 17.0 us
+// in passes and 15.3 so, of 155 17.6 and 19.2; 2 x 256 of 100 4.8 and 4.3). More: where the groups fill the CUs and the blocks, of about 5 bits a symbol, at least three
 // quarters of the waves' rounds (1536-token chunks, eight blocks: 1024 groups 32.4 and 29.1, 28160
 // 645 and 623, but 256 13.5 and 14.2; 256 tokens, two blocks: 3072 groups 22.6 and 24.4). Token
 // streams differ in length (an anchor token's symbols take 7 to 8 bits) and stay with the passes
@@ -1302,8 +1302,9 @@ __global__ __launch_bounds__(256) void compact_kernel(KParams P, const uint32_t*
 bool compact_own(const KParams& P, bool tok, int64_t groups) {
   if (tok) return P.C <= 128;
   const int64_t n = P.CL < P.T ? P.CL : P.T;
+  if (n * 7 <= 1024) return true;
   const int64_t nb = (n * 5 + 1023) / 1024;
-  return nb <= 1 || (groups >= 1024 && nb >= (nb + 3) / 4 * 3);
+  return groups >= 1024 && nb >= (nb + 3) / 4 * 3;
 }
 
 inline uint64_t align256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
