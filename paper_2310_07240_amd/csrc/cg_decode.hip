@@ -1889,13 +1889,17 @@ hipError_t cg_launch_decode(const KParams& P, const uint32_t* words, const uint6
     auto piece_lds = [&](int w, int un) {
       return (size_t)un * (w * kG10 * 64 + (w < P.NLV ? w : P.NLV) * kPieceSet) * sizeof(uint16_t);
     };
-    // (Short chunks too, where staging the tables is much of the time and fewer pairs share them: 6
-    // contexts x 4 layers x 64 channels of 12, 20 and 39 tokens 28.5, 30.1 and 37.7 us otherwise and
-    // 25.5, 26.2 and 32.2 here, 32 contexts at four levels 35, 39 and 50, here 25, 27 and 33.)
+    // (Chunks of under 40 tokens too, where staging the tables is much of the time, but not several
+    // units of several pairs, which would stage each unit's tables once per pair: 6 contexts x 4
+    // layers x 64 channels of 12, 20 and 39 tokens 28.5, 30.1 and 37.7 us otherwise and 25.5, 26.2 and
+    // 32.2 here, 32 contexts at four levels 35, 39 and 50, here 25, 27 and 33; but 3 contexts x 80 layers x
+    // 128 channels of 29 tokens, four units of one pair, 23.5 otherwise and 28.4 here.)
+    const int n_max = P.CL < P.T ? P.CL : P.T;
     for (int waves = 1; waves <= 4 && !pnw; ++waves)
       for (int w = 1; w <= waves && w <= n_pairs; ++w) {
         const int un = waves / w;
         if (un * w == waves && piece_lds(w, un) <= kLdsBudget &&
+            (un == 1 || n_pairs == 1 || n_max >= 40) &&
             (n_units + un - 1) / un * ((n_pairs + w - 1) / w) <= 256) {
           pnw = w;
           pnu = un;   // the last fit: more pairs of a unit share its tables

@@ -45,6 +45,7 @@ def decode_stage(w, n_pairs=None):
         for pw in range(1, min(waves, pairs) + 1):
             pu = waves // pw
             if (pu * pw == waves and piece_lds(pw, pu) <= LDS_BUDGET
+                    and (pu == 1 or pairs == 1 or min(w.chunk_len, w.n_tokens) >= 40)
                     and -(-units // pu) * -(-pairs // pw) <= 256):
                 return "pieces", waves
     if sets > 1 and nuc > nu:
@@ -155,6 +156,7 @@ def test_symbols_outside_the_searched_blocks(bin_, n_layers, n_channels, n_token
     (1, 17, 2048, 21, 21, (1.0, 2.0)),      # 1088 waves of one pair
     (6, 4, 72, 25, 12, (1.0, 4.0)),         # chunks of 12 tokens and one
     (16, 32, 64, 11, 11, (1.0,)),           # 1024 waves: four pairs of a unit
+    (3, 80, 128, 29, 29, (1.0,)),           # 960 waves: three pairs of a unit
 ])
 def test_at_most_a_wave_per_simd(n_ctx, n_layers, n_channels, n_tokens, chunk_len, levels):
     torch = torch_cuda()
