@@ -1053,7 +1053,8 @@ __global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024)
   // Where the grid is one round on the CUs, its slowest workgroup is its end: a workgroup's units
   // then come from different layers (unit u from the u-th part of the units, every second part
   // backwards), so that deep layers, whose symbols take fewer instructions (see g10_blocks),
-  // share every CU and SIMD with shallow ones (Mistral-7B-shaped 4K cache: 515 us, 527 without).
+  // share every CU and SIMD with shallow ones (Mistral-7B-shaped 4K cache: a decode on its own 599 us,
+  // 610 without; back to back no difference, 537 to 546 us either way).
   // Else, and where blocks of 64 channels share cache lines with their neighbours, neighbouring
   // units: their rows are stored together (384 workgroups of 4096 channels: 763 us, 804 mixed).
   const bool mix = !kCompact && (P.C & 63) == 0 && gridDim.x <= 256u;
@@ -1881,8 +1882,8 @@ hipError_t cg_launch_decode(const KParams& P, const uint32_t* words, const uint6
       ++nuc;
     // Up to one wave per SIMD (a chunk of a cache as it arrives, a short context), the time is the
     // latency of the symbols' chain: the piece layout takes one LDS round trip per symbol instead
-    // of three (the second chunk of a Mistral-7B-shaped cache, 1024 waves: 472 -> 399 us; 16 waves
-    // of 256 tokens: 91 -> 77 us). With two waves per SIMD they hide each other's round trips
+    // of three (the second chunk of a Mistral-7B-shaped cache, 1024 waves: 474 -> 384 us; 16 waves
+    // of 256 tokens: 92 -> 77 us). With two waves per SIMD they hide each other's round trips
     // and the search with fewer instructions is the faster one. The smallest workgroups that
     // make one round on 256 CUs, at most four decoding waves each: pnw pairs x pnu units.
     int pnw = 0, pnu = 0;

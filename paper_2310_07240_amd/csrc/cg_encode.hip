@@ -846,8 +846,10 @@ __global__ __launch_bounds__(kScanThreads) void scan_finish(const uint32_t* __re
 }
 
 // The whole scan in one workgroup, for a few thousand streams: tiles of 4096 word counts (four
-// per thread) in order, the status word as scan_top's. Three launches took 13.5 us for the 1024
-// streams of a short context, this 4.7.
+// per thread) in order, the status word as scan_top's. One launch instead of three; past the line
+// below one workgroup's tiles in a row take longer than the launches saved (whole encode calls of 256
+// tokens, one launch and three: 1024 streams 85.6 and 91.2 us, 8192 88.6 and 96.3, 16384 93.3 and 96.2,
+// 32768 106.2 and 104.2, 65536 125.5 and 110.3).
 constexpr int kScanOne = 16384;   // streams
 __global__ __launch_bounds__(1024) void scan_one(const uint32_t* __restrict__ lens, int S,
                                                  uint64_t* __restrict__ offsets,
@@ -1294,9 +1296,10 @@ __global__ __launch_bounds__(256) void compact_kernel(KParams P, const uint32_t*
 // Whether the compaction's waves take blocks of their own (kOwn), by the symbols of a stream (tokens
 // of a chunk, or channels) and the launch's groups. One block of 32 words per stream, of the longest
 // in each group at about 7 bits a symbol: always (2 x 48 layers x 1024 channels of 140 tokens 17.0 us
-// in passes and 15.3 so, of 155 17.6 and 19.2; 2 x 256 of 100 4.8 and 4.3). More: where the groups fill the CUs and the blocks, of about 5 bits a symbol, at least three
-// quarters of the waves' rounds (1536-token chunks, eight blocks: 1024 groups 32.4 and 29.1, 28160
-// 645 and 623, but 256 13.5 and 14.2; 256 tokens, two blocks: 3072 groups 22.6 and 24.4). Token
+// in passes and 15.3 so, of 155 17.6 and 19.2; 2 x 256 of 100 4.8 and 4.3). More: where the groups
+// fill the CUs and the blocks, of about 5 bits a symbol, at least three quarters of the waves' rounds
+// (1536-token chunks, eight blocks: 1024 groups 32.4 and 29.1, 28160 645 and 623, but 256 13.5 and
+// 14.2; 256 tokens, two blocks: 3072 groups 22.6 and 24.4). Token
 // streams differ in length (an anchor token's symbols take 7 to 8 bits) and stay with the passes
 // (256 channels, 4608 groups: 32.1 and 35.8; 1024: 82 and 86).
 bool compact_own(const KParams& P, bool tok, int64_t groups) {
@@ -1365,9 +1368,12 @@ EncGeom enc_geometry(const KParams& P, bool spread = true) {
   }
   // Few waves in workgroups of more than four (several on a SIMD while other CUs have none): the
   // smallest workgroups that make one round on 256 CUs instead, as the decoder's (240 waves of
-  // 1536 tokens in 40 workgroups of six: 607 us, now 385). Short chunks are left: their time is
-  // the staging of tables, which the pairs of a unit share. And up to one wave per SIMD, helpers
-  // stage the tables (16 waves of 256 tokens: 67 us, now 61).
+  // 1536 tokens in 40 workgroups of six: 607 us, now 385). Chunks of under 40 tokens are left: most of
+  // their time is the staging of tables, which the pairs of a unit share. With the call's own scales,
+  // together and spread: 6 contexts x 4 layers x 64 channels, 20 tokens 40.5 and 45.1 us, 60 tokens 51.2
+  // and 52.6; 16 contexts at two levels 57.4 and 51.2, 73.7 and 59.6. With given scales, whose helpers
+  // stage the tables, 20 tokens 38.2 and 36.8, 53.6 and 42.8: a line by tokens alone that gives up some of
+  // these. And up to one wave per SIMD, helpers stage the tables (16 waves of 256 tokens: 67 us, now 61).
   const bool few = spread && n_units * n_pairs <= 4 * 256;
   if (few && g.nw * g.nu > 4 && (n_pairs == 1 || (P.CL < P.T ? P.CL : P.T) >= 40)) {
     for (int waves = 1; waves <= 4; ++waves) {
