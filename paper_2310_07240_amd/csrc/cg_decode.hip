@@ -1560,8 +1560,8 @@ __global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024)
 // one (context, chunk, layer, K/V), stage kTokTile channels' anchor and delta tables in LDS
 // together, the next tile's loads in flight while one is decoded (staged by every wave for
 // itself and one channel ahead, each symbol waited for its tables to arrive: 1.70 ms for a
-// Mistral-7B-shaped 4K cache, now 0.74, VALU busy 0.83 with 78 instructions per symbol). A table is its 256 entries (255 on repeating cum[254])
-// and its 16 fences cum[16 f] once more; a symbol reads the fences (the same for all lanes of a
+// Mistral-7B-shaped 4K cache, now 0.74, VALU busy 0.80 with 78 instructions per symbol). A table
+// is its 256 entries (255 on repeating cum[254]) and its 16 fences cum[16 f] once more; a symbol reads the fences (the same for all lanes of a
 // kind, and their address is known ahead), then its block of 16 entries, and searches both
 // with selects on registers, as the piece layout does. Symbols collect in a row per token in
 // LDS and go to the symbol array [B][L][2][T][C] every 64 channels; tok_dequant_kernel
