@@ -314,7 +314,7 @@ inline bool cg_tok_octets(const KParams& P, const void* p) {
   if (P.C % 8 != 0 || (reinterpret_cast<uintptr_t>(p) & 15) != 0) return false;
   const int64_t n = P.CL < P.T ? P.CL : P.T;
   const int64_t ng = (n + P.G - 1) / P.G;
-  return ng == 1 ? n < 64 || P.G == 10 : ng > 8 || P.G <= 200;
+  return ng == 1 ? n < 64 : ng > 8 || P.G <= 200;
 }
 // Launch geometry of the token layout's row kernels (tok_quantize_kernel, tok_dequant_kernel). A
 // workgroup takes 128 (octets) or 64 channels of one (context, chunk, layer, K/V) in 16 or 64
