@@ -1882,8 +1882,8 @@ hipError_t cg_launch_decode(const KParams& P, const uint32_t* words, const uint6
       ++nuc;
     // Up to one wave per SIMD (a chunk of a cache as it arrives, a short context), the time is the
     // latency of the symbols' chain: the piece layout takes one LDS round trip per symbol instead
-    // of three (the second chunk of a Mistral-7B-shaped cache, 1024 waves: 474 -> 384 us; 16 waves
-    // of 256 tokens: 92 -> 77 us). With two waves per SIMD they hide each other's round trips
+    // of three (the second chunk of a Mistral-7B-shaped cache, 1024 waves: 472 -> 384 us; 16 waves
+    // of 256 tokens: 91 -> 73 us). With two waves per SIMD they hide each other's round trips
     // and the search with fewer instructions is the faster one. The smallest workgroups that
     // make one round on 256 CUs, at most four decoding waves each: pnw pairs x pnu units.
     int pnw = 0, pnu = 0;
