@@ -1121,7 +1121,8 @@ hipError_t launch_fit_pass(const KParams& P, const uint16_t* kv, int lv0, int nl
 // there), the tables at the end less, and where there are fewer blocks than CUs nothing hides it.
 // 2 layers x 66 channels, one level, there over here: 8 contexts of 16 to 80 tokens 1.02 to 1.10, 12
 // of 16 and 45 0.94 and 1.00, 16 of 29 and 45 0.90 and 0.95, 32 of 29, 45 and 80 0.81, 0.87 and 0.92;
-// 80 layers x 160 channels, 32 contexts of 21, 40 and 60 0.92, 0.98 and 1.03. Two levels: 0.93 to 0.96
+// 80 layers x 160 channels, 32 contexts of 21, 40 and 60 0.92, 0.98 and 1.03, 16 of 9, 12 and 25 0.90, 0.98
+// and 1.05. One group, 4 contexts of 5 tokens from 1.00 on, 8 0.90, 16 0.76 to 0.83. Two levels: 0.93 to 0.96
 // for two groups, from 0.99 on for three (30 layers x 480 channels, two groups 1.00 to 1.16). Three and
 // five to seven levels: two groups 0.92, four 0.94 to 1.03, 16 1.05.
 bool fit_ragged_pass(const KParams& P) {
@@ -1132,7 +1133,10 @@ bool fit_ragged_pass(const KParams& P) {
     const bool fills = (int64_t)P.L * 2 * P.nblk > 256;
     const int64_t pairs = (int64_t)P.B * P.NC;
     if (fewer || ng > 8) return true;
-    if (P.NLV == 1) return fills ? ng > 3 || pairs < 24 : pairs < (ng <= 3 ? 10 : ng <= 5 ? 14 : 20);
+    if (P.NLV == 1) {
+      if (ng == 1) return pairs < 6;
+      return fills ? ng > 3 || pairs < 8 * ng : pairs < (ng <= 3 ? 10 : ng <= 5 ? 14 : 20);
+    }
     return P.NLV == 2 ? ng > 2 || fills : ng > 4;
   }
   if (ng > kFitWaves) return true;

@@ -33,6 +33,8 @@ L5 = (1.0, 2.0, 4.0, 8.0, 16.0)
     (70, 41, 41, (1.0, 2.0, 4.0), 10, 0),
     (66, 51, 51, L5[:4], 17, 0),            # three groups and two
     (66, 34, 34, L5[:4], 17, 0),
+    (66, 20, 10, (1.0,), 10, 0),            # 4 chunks of one group, and 8
+    (66, 40, 10, (1.0,), 10, 0),
     (66, 200, 20, (1.0,), 10, 0),           # 20 chunks of two groups, 10 of four
     (66, 200, 40, (1.0,), 10, 0),
     (66, 40, 20, (1.0, 2.0), 10, 0),        # two groups at two levels, and three
