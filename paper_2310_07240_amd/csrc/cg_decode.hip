@@ -604,7 +604,9 @@ struct ColTab {   // all 256 entries in LDS, column layout
 
 // All 256 entries in LDS in 16-byte pieces: entries 8 m .. 8 m + 7 of the lane in column L at byte
 // 16 (64 m + L) of its set, so that a wave's 16-byte reads at 64 different pieces do not
-// collide in the banks. g10_symbol returns the symbol itself for this table.
+// collide in the banks. g10_symbol returns the symbol itself for this table, and with kFar keeps the
+// walk outside the loop.
+template <bool kFar>
 struct PieceTab {
   static constexpr uint32_t kS = 128;   // per entry of a whole number of pieces
   uint32_t tb;                          // byte address of the lane's piece 0
@@ -713,6 +715,11 @@ __device__ __forceinline__ void g10_fences_win(uint32_t (&fT)[kF], const WinTab&
 constexpr uint32_t kOutCost = 250;
 // fewest tokens of a chunk for which the choice pays (it takes about a microsecond)
 constexpr int kNarrowMin = 256;
+// Fewest tokens of a chunk for which the piece layout's walk lies outside the loop: the first walks of
+// a wave then wait for instructions (3 contexts x 1 layer x 5120 channels, inside and outside: 45
+// tokens 30.0 and 31.0 us, 65 37.6 and 38.6, 130 56.5 and 57.8, 300 101.2 and 100.8; the second chunk of
+// a Mistral-7B-shaped cache, 1536 tokens, 400 and 384).
+constexpr int kFarMin = 256;
 template <class Tab>
 __device__ __forceinline__ int g10_blocks(const Tab& T, int n_ctx, int& k0) {
   const int med = g10_find(T, 32768u);
@@ -910,11 +917,12 @@ __device__ __forceinline__ uint32_t find16(const u32x4& a, const u32x4& b, uint3
 // runs one wave, see cg_launch_decode): the block's 16 entries and the one after them come
 // in one LDS round trip, and the search and the candidate's bounds are selects on registers (one
 // round trip per symbol instead of three, for about eight more instructions). Returns the symbol.
+template <bool kFar>
 __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)[16],
-                                               const PieceTab& T) {
+                                               const PieceTab<kFar>& T) {
   typedef __attribute__((address_space(3))) const u32x4 lds_cu32x4;
   const uint32_t th = g10_target(st), ti = th >> 16;
-  const uint32_t qa = g10_block(fT, th, T.tb, PieceTab::kS);
+  const uint32_t qa = g10_block(fT, th, T.tb, T.kS);
   const u32x4 e03 = *(lds_cu32x4*)(uintptr_t)qa, e47 = *(lds_cu32x4*)(uintptr_t)(qa + 1024u);
   const uint32_t e8 = lds_ld16(qa + 2048u);
   uint32_t pl, pn;
@@ -927,7 +935,7 @@ __device__ __forceinline__ uint32_t g10_symbol(G10Lane& st, const uint32_t (&fT)
   uint32_t hoff = __umulhi(R, pair & 0xFFFF0000u);
   uint32_t d = D - lo_off;
   uint32_t rsz = hoff - lo_off;
-  if (__builtin_expect(__builtin_amdgcn_ballot_w64(d >= rsz) != 0, 0)) if (d >= rsz) {
+  if (!kFar || __builtin_expect(__builtin_amdgcn_ballot_w64(d >= rsz) != 0, 0)) if (d >= rsz) {
     const int nxt = R == 0u ? g10_find(T, D >> 16) : T.first((int)sym, ti, D < lo_off);
     sym = (uint32_t)g10_walk(T, D, R, nxt, lo_off, hoff, d, rsz);
   }
@@ -1012,15 +1020,18 @@ __device__ __forceinline__ void g10_flush_full(const uint16_t* obuf, uint16_t* r
 // and then the windows of its delta tables, packed; sets that do not fit together are staged in
 // rounds, one after the other. Otherwise the region holds min(nw, levels) whole sets.
 // kPiece: whole sets in the piece layout, for calls of at most one wave per SIMD; the workgroup
-// then has more waves than the nu nw that decode (helpers: they only stage tables).
-enum class Stage { kColumns, kWindows, kPieces };
+// then has more waves than the nu nw that decode (helpers: they only stage tables). kShortPieces: the
+// same for short chunks, with the walk inside the loop (see kFarMin).
+enum class Stage { kColumns, kWindows, kPieces, kShortPieces };
+constexpr bool is_pieces(Stage s) { return s == Stage::kPieces || s == Stage::kShortPieces; }
 template <Stage kStage>
-__global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024) void decode_g10_kernel(
+__global__ __launch_bounds__(is_pieces(kStage) ? 64 * kPieceWaves : 1024) void decode_g10_kernel(
     KParams P, const uint32_t* __restrict__ words, const uint64_t* __restrict__ offsets,
     const float* __restrict__ scales, const uint8_t* __restrict__ chunk_level,
     const uint16_t* __restrict__ cdfA, const uint16_t* __restrict__ cdfD, int c_begin,
     int c_end, int nw, int nu, int ustride, uint16_t* __restrict__ out) {
-  constexpr bool kCompact = kStage == Stage::kWindows, kPiece = kStage == Stage::kPieces;
+  constexpr bool kCompact = kStage == Stage::kWindows, kPiece = is_pieces(kStage);
+  using Pieces = PieceTab<kStage == Stage::kPieces>;
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   __shared__ int s_wlv[kMaxWaves];               // bit of the level of each wave's pair (0: none)
   __shared__ uint8_t s_set_of_level[kMaxUnits][CG_MAX_LEVELS];
@@ -1349,7 +1360,7 @@ __global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024)
     w = P.layer_bin[l] * P.level_mult[lv] * s;
     uint32_t fA[16];   // tagged fences of the anchor table
     const auto TA = [&] {
-      if constexpr (kPiece) return PieceTab{lds_addr(tab0)};
+      if constexpr (kPiece) return Pieces{lds_addr(tab0)};
       else return ColTab(tab0);
     }();
     g10_fences(fA, TA, 0);
@@ -1530,7 +1541,7 @@ __global__ __launch_bounds__(kStage == Stage::kPieces ? 64 * kPieceWaves : 1024)
       else if (full) groups_of(std::integral_constant<int, 16>{}, std::true_type{});
       else groups_of(std::integral_constant<int, 16>{}, std::false_type{});
     } else if constexpr (kPiece) {
-      const PieceTab T{lds_addr(tabs + u * ustride + set * kPieceSet + 8 * lsrc)};
+      const Pieces T{lds_addr(tabs + u * ustride + set * kPieceSet + 8 * lsrc)};
       uint32_t fD[16];
       g10_fences(fD, T, 0);
       if (full) delta_groups(T, fD, std::true_type{});
@@ -1936,7 +1947,8 @@ hipError_t cg_launch_decode(const KParams& P, const uint32_t* words, const uint6
     }
     const int64_t grid = cg_xcd_grid((n_units + units - 1) / units,
                                      (n_pairs + pairs_wg - 1) / pairs_wg);
-    const auto kernel = piece     ? &decode_g10_kernel<Stage::kPieces>
+    const auto kernel = piece     ? n_max >= kFarMin ? &decode_g10_kernel<Stage::kPieces>
+                                                     : &decode_g10_kernel<Stage::kShortPieces>
                         : compact ? &decode_g10_kernel<Stage::kWindows>
                                   : &decode_g10_kernel<Stage::kColumns>;
     hipError_t e = hipFuncSetAttribute((const void*)kernel,
